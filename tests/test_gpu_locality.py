@@ -50,6 +50,21 @@ def test_exact_knn(shape, causal):
     assert np.array_equal(got[:, rows], want)
 
 
+@pytest.mark.parametrize("N,kn", [(64, 64), (65, 64), (513, 1), (2048, 63), (2048, 64), (2048, 65), (4096, 64)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_exact_knn_ties(N, kn, causal):
+    """Coordinates from three values: hundreds of keys at each distance, so
+    positions decide and the candidates of one query outnumber the kernel's
+    list of them; kn on both sides of the wavefront search's largest."""
+    log(f"exact knn ties N={N} kn={kn} causal={causal}")
+    rng = np.random.default_rng([N, kn])
+    q, k = (rng.integers(0, 3, size=(1, 2, N, 3)).astype(np.float32) for _ in range(2))
+    got = host(zeta.zeta_exact_knn(to_dev(q, "f32"), to_dev(k, "f32"), kn, causal)).reshape(2, N, kn)
+    rows = np.unique(np.r_[np.arange(min(N, 70)), np.linspace(0, N - 1, 100).astype(int)])
+    want = oracle.exact_knn(q.reshape(2, N, 3), k.reshape(2, N, 3), kn, causal, rows=rows)
+    assert np.array_equal(got[:, rows], want)
+
+
 def test_index_overlap():
     log("index overlap")
     rng = np.random.default_rng(3)

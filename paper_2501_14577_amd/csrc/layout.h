@@ -38,6 +38,15 @@ constexpr int64_t kLevelTile = 2048;
 // Up to this many tiles per segment the scatter sums the earlier tiles' counts
 // itself; beyond it a scan kernel writes them first.
 constexpr int64_t kRadixInlineTiles = 32;
+// Whether a workgroup sorts each segment whole (one launch) instead of tiled
+// passes over the chip.  Up to 8192 keys always: the passes' launches cost more
+// whatever the number of segments (45 us against 26 for 64 segments of 30-bit
+// codes).  Up to 16384 keys only when the segments fill a good part of the 256
+// CUs: 100 segments or more gain (256: 102 -> 50 us), 16 are even (44, 43 us)
+// and lose on 18-bit codes and the level partition (23 -> 25, 12 -> 14 us).  At
+// 32768 keys a workgroup's registers spill and it loses at any number (46 ->
+// 100 us for 16 segments).
+inline bool block_sort_path(int64_t S, int64_t N) { return N <= 8192 || (N <= 16384 && S >= 100); }
 
 // ---- select ---------------------------------------------------------------
 constexpr int kMaxLevels = 32;

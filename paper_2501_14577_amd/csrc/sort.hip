@@ -18,6 +18,9 @@
 //            consecutive addresses.
 // Tiles of one segment run on one XCD (xcd_contiguous_block): the runs
 // several tiles write into the same output lines merge in that XCD's L2.
+// Segments of up to 8192 keys (16384 when there are many; block_sort_path)
+// take one launch instead: a workgroup holds a whole segment in registers and
+// runs every pass on it (block_sort).
 // A pass preserves the order of equal digits, so after the last pass equal
 // codes are in ascending position order.  ceil(code_bits / 9) passes split
 // the bits evenly (18-bit codes: two passes of 9).
@@ -271,6 +274,168 @@ __global__ void __launch_bounds__(kRadixThreads)
   }
 }
 
+// ---- whole segments in one workgroup ---------------------------------------------
+// A segment of at most THREADS * KPT keys, one workgroup: thread registers
+// hold the keys (and positions), every pass ranks them as radix_scatter does
+// (per wavefront, 64 keys at a time) and moves them through LDS.  No tile
+// counts go through memory and the passes need no launches of their own.
+// Elements past the segment's end carry an all-ones key: they stay last in
+// every pass.  kByLevel: one pass over the level class of the carried
+// positions (the level partition of a processing order), which are the keys
+// here and the only output.
+//
+// Bound: one CU's vector issue and LDS latency (a pass costs a wavefront KPT
+// times about 45 instructions and a dependent LDS count, and 4 barriers); most
+// of the chip idles when there are few segments, yet the launches it replaces
+// cost more.  Measured, 30-bit codes, tiled passes -> this kernel: 2048 keys x
+// 256 segments 42.7 -> 13.3 us, 8192 x 64 45 -> 27, 8192 x 512 100 -> 56; the
+// level partition, 8192 x 256, 18.8 -> 10.7.
+template <int THREADS, int KPT, bool kByLevel>
+__global__ void __launch_bounds__(THREADS)
+    block_sort_kernel(const uint32_t* __restrict__ keys, const int32_t* __restrict__ vals, int64_t N, int code_bits,
+                      int digit_bits, int t0, int t_hi, int chunk, uint32_t* __restrict__ keys_out,
+                      int32_t* __restrict__ pos_out) {
+  constexpr int kWaves = THREADS / 64;
+  constexpr int kCap = THREADS * KPT;
+  static_assert(kCap <= 16384, "positions, slots and counts are 16-bit, keys and positions fit LDS");
+  __shared__ __align__(16) uint32_t s_key[kCap];
+  __shared__ uint16_t s_pos[kByLevel ? 1 : kCap];
+  __shared__ uint16_t s_cnt[kWaves][kRadixMax];
+  __shared__ uint32_t s_scan[kWaves];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int64_t off = int64_t(blockIdx.x) * N;
+  const int n = int(N);
+  const int first = wave * (KPT * 64) + lane;  // element c of this thread: first + 64 c
+
+  uint32_t key[KPT];
+  uint32_t pos[KPT];  // position in the low half, rank in the high half
+#pragma unroll
+  for (int c = 0; c < KPT; ++c) {
+    const int e = first + c * 64;
+    const int ec = e < n ? e : n - 1;
+    if (kByLevel)
+      key[c] = vals != nullptr ? uint32_t(vals[off + ec]) : uint32_t(ec);
+    else
+      key[c] = keys[off + ec];
+    pos[c] = uint32_t(e);
+  }
+  if (!kByLevel) {
+#pragma unroll
+    for (int c = 0; c < KPT; ++c) key[c] = first + c * 64 < n ? key[c] : ~0u;
+  }
+
+  for (int shift = 0; shift < code_bits; shift += digit_bits) {
+    const int nbits = code_bits - shift < digit_bits ? code_bits - shift : digit_bits;
+    const uint32_t mask = (1u << nbits) - 1u;
+    auto digit = [&](int c) -> uint32_t {
+      if (kByLevel) {
+        const uint32_t d = radix_digit<true>(0u, int32_t(key[c]), 0, 0u, t0, t_hi, chunk, N);
+        return (pos[c] & 0xFFFFu) < uint32_t(n) ? d : mask;
+      }
+      return (key[c] >> shift) & mask;
+    };
+    // Counts of the pass's digit values, cleared two at a time.
+    for (int i = tid; i < kWaves * kRadixMax / 2; i += THREADS) reinterpret_cast<uint32_t*>(&s_cnt[0][0])[i] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < KPT; ++c) {
+      const uint32_t d = digit(c);
+      uint32_t plo = ~0u, phi = ~0u;
+#pragma unroll
+      for (int b = 0; b < kDigitBits; ++b) {
+        if (b < nbits) {
+          const uint32_t s = uint32_t(int32_t(d << (31 - b)) >> 31);
+          const uint64_t ones = wave_ballot(s != 0u);
+          plo = __builtin_amdgcn_bitop3_b32(plo, uint32_t(ones), s, 0x90);
+          phi = __builtin_amdgcn_bitop3_b32(phi, uint32_t(ones >> 32), s, 0x90);
+        }
+      }
+      const uint64_t peers = (uint64_t(phi) << 32) | plo;
+      const uint32_t below = lanes_below(peers);
+      const uint32_t base = s_cnt[wave][d];
+      if (below == 0) s_cnt[wave][d] = uint16_t(base + uint32_t(__popcll(peers)));
+      pos[c] = (pos[c] & 0xFFFFu) | ((base + below) << 16);
+    }
+    __syncthreads();
+    {
+      // First slot of each (digit value, wavefront): 512 values over the
+      // block's threads, kPer of them each.
+      constexpr int kPer = (kRadixMax + THREADS - 1) / THREADS;
+      uint32_t tot[kPer], sum = 0;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        const int d = tid * kPer + j;
+        tot[j] = 0;
+        if (d < kRadixMax) {
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) tot[j] += s_cnt[w][d];
+        }
+        sum += tot[j];
+      }
+      uint32_t run = block_exclusive_scan<kWaves>(sum, s_scan);
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        const int d = tid * kPer + j;
+        if (d < kRadixMax) {
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) {
+            const uint32_t t = s_cnt[w][d];
+            s_cnt[w][d] = uint16_t(run);
+            run += t;
+          }
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < KPT; ++c) {
+      const uint32_t slot = s_cnt[wave][digit(c)] + (pos[c] >> 16);
+      s_key[slot] = key[c];
+      if constexpr (!kByLevel) s_pos[slot] = uint16_t(pos[c]);
+    }
+    __syncthreads();
+    const bool last = shift + digit_bits >= code_bits;
+    if constexpr (kByLevel) {
+      for (int i = tid; i < n; i += THREADS) pos_out[off + i] = int32_t(s_key[i]);
+    } else if (last) {
+      for (int i = tid; i < n; i += THREADS) {
+        keys_out[off + i] = s_key[i];
+        pos_out[off + i] = int32_t(s_pos[i]);
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < KPT; ++c) {
+        key[c] = s_key[first + c * 64];
+        pos[c] = s_pos[first + c * 64];
+      }
+    }
+    // The next pass writes s_key only after its own barriers.
+  }
+}
+
+// Threads and keys per thread by segment length: enough threads to keep the
+// per-thread chain short, few enough that several short segments share a CU.
+template <bool kByLevel>
+void launch_block_sort(const uint32_t* keys, const int32_t* vals, int64_t S, int64_t N, int code_bits, int digit_bits,
+                       int t0, int t_hi, int chunk, uint32_t* keys_out, int32_t* pos_out, hipStream_t stream) {
+#define ZETA_BLOCK_SORT(THREADS, KPT)                                                                             \
+  hipLaunchKernelGGL((block_sort_kernel<THREADS, KPT, kByLevel>), dim3(unsigned(S)), dim3(THREADS), 0, stream, keys, \
+                     vals, N, code_bits, digit_bits, t0, t_hi, chunk, keys_out, pos_out)
+  if (N <= 1024)
+    ZETA_BLOCK_SORT(512, 2);
+  else if (N <= 2048)
+    ZETA_BLOCK_SORT(512, 4);
+  else if (N <= 4096)
+    ZETA_BLOCK_SORT(1024, 4);
+  else if (N <= 8192)
+    ZETA_BLOCK_SORT(1024, 8);
+  else
+    ZETA_BLOCK_SORT(1024, 16);
+#undef ZETA_BLOCK_SORT
+}
+
 // One pass over tiles of kRadixThreads * kChunks keys: hist, [scan,] scatter.
 template <bool kHasPos, bool kByLevel, int kChunks>
 void radix_pass(const uint32_t* keys_in, const int32_t* pos_in, int64_t S, int64_t N, int64_t tiles, int shift,
@@ -301,6 +466,10 @@ hipError_t launch_level_partition(const int32_t* vals, int64_t S, int64_t N, int
   const int64_t tiles = ceil_div(N, kLevelTile);
   int nbits = 1;
   while ((1 << nbits) < levels + 1) ++nbits;
+  if (block_sort_path(S, N)) {
+    launch_block_sort<true>(nullptr, vals, S, N, nbits, nbits, t0, t_hi, chunk, nullptr, vals_out, stream);
+    return hipGetLastError();
+  }
   if (vals != nullptr)
     radix_pass<true, true, kChunks>(nullptr, vals, S, N, tiles, 0, nbits, t0, t_hi, chunk, hist, nullptr, vals_out,
                                     stream);
@@ -313,6 +482,10 @@ hipError_t launch_level_partition(const int32_t* vals, int64_t S, int64_t N, int
 hipError_t launch_sort(const uint32_t* k_codes, int64_t S, int64_t N, int code_bits,
                        uint32_t* sorted_codes, int32_t* perm, void* workspace, hipStream_t stream) {
   const SortPlan plan = sort_plan(N, code_bits);
+  if (block_sort_path(S, N)) {
+    launch_block_sort<false>(k_codes, nullptr, S, N, code_bits, plan.digit_bits, 0, 0, 0, sorted_codes, perm, stream);
+    return hipGetLastError();
+  }
   const SortWs ws = sort_ws(S, N, code_bits);
   char* wsb = static_cast<char*>(workspace);
   uint32_t* hist = reinterpret_cast<uint32_t*>(wsb + ws.hist_off);

@@ -140,6 +140,39 @@ def test_sort_shapes(S, N, code_bits):
     assert np.array_equal(host(sc), esc)
 
 
+@pytest.mark.parametrize("N", [1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 16384, 16385])
+@pytest.mark.parametrize("S", [2, 100])
+def test_sort_and_order_workgroup_edges(N, S):
+    """The last and first segment lengths of each workgroup size of the
+    whole-segment sort, and of the tiled passes: one to four passes, codes
+    whose every bit is set (the value that pads a segment) and heavy
+    duplicates; the level partition at the same lengths, in place too."""
+    if S > 2 and N < 8192:
+        pytest.skip("the number of segments decides beyond 8192 keys only")
+    log(f"sort and order edges N={N} S={S}")
+    rng = np.random.default_rng(N)
+    for code_bits in (1, 9, 18, 32) if S == 2 else (32,):
+        kc = workloads.random_codes(N + code_bits, (S, N), code_bits)
+        kc[:, rng.integers(0, N, N // 8)] = (1 << code_bits) - 1
+        esc, eperm = oracle.sort_keys(kc)
+        sc, perm = zeta.zeta_sort_keys(u32_to_dev(kc), code_bits)
+        torch.cuda.synchronize()
+        assert np.array_equal(host(perm), eperm)
+        assert np.array_equal(host(sc), esc)
+    z = np.stack([rng.permutation(N) for _ in range(S)]).astype(np.int32)
+    z[:, rng.integers(0, N, 9)] = [-1, N, -2 ** 31, 2 ** 31 - 1, N + 7, -5, N, -1, 0]
+    dev = i32_to_dev(z)
+    got = zeta.zeta_query_order(dev, N, S, 16, True, chunk=N // 5)
+    same = zeta.zeta_query_order(dev, N, S, 16, True, chunk=N // 5, order_out=dev)
+    torch.cuda.synchronize()
+    lim = np.where((z < 0) | (z >= N), -1, z) // (N // 5) * (N // 5) - 1  # out-of-range entries go with the first level
+    bits = np.ceil(np.log2(np.maximum(lim, 0) + 1)).astype(int)  # bit length of the largest pool position
+    level = np.minimum(np.maximum(bits, 4), (N - 1).bit_length())
+    want = np.take_along_axis(z, np.argsort(level, axis=1, kind="stable"), axis=1)
+    assert np.array_equal(host(got), want)
+    assert np.array_equal(host(same), want)
+
+
 @pytest.mark.parametrize("S,N,code_bits,high_values", [(2, 20000, 18, 4), (1, 9000, 18, 1), (3, 4097, 16, 2)])
 def test_sort_clustered(S, N, code_bits, high_values):
     """Codes whose high digit takes only a few values (one value: every key

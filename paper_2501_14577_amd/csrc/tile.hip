@@ -105,12 +105,18 @@ constexpr uint32_t kIdxEmpty = 0xFFFFFFFFu;
 // left side runs out.
 //
 // Consecutive slots search one list at nearby insertion points.  The list
-// range of kRegion entries around the run's first insertion point is copied
-// to LDS (codes and positions); a lane reads the list itself only outside it
-// or when its query searches another list.
+// range of kRegion entries around the first waiting query's insertion point is
+// copied to LDS (codes and positions) and serves every lane of that list near
+// it; the others wait for a range of their own, or, in an order without
+// locality, read the lists themselves.  Bound: vector issue when there are many
+// runs, else the latency of the slowest run: with the other lanes served by one
+// wavefront-wide search each, a run that crosses two lists held the call up by
+// 10-30 us (1024 queries, k 32: 25 -> 9 us; 8 x 20011, k 64: 66 -> 34 us; clustered
+// keys, 128 x 4096, k 64, not causal: 46 -> 25 us; runs of one list, 16 x 65536,
+// k 128: 42 us either way).
 constexpr int kBndWaves = 4;
-constexpr int kRegion = 512;   // list entries staged per wavefront (a multiple of 32)
-constexpr int kMargin = 192;    // of them before the run's first insertion point (about)
+constexpr int kRegion = 640;   // list entries staged per wavefront (a multiple of 64; 512 left more runs a second round)
+constexpr int kMargin = 192;    // at most this many of them before the leading insertion point
 
 // Each wavefront's copy of a list range, in LDS.  Declared at file scope and
 // indexed directly, so that every access compiles to an LDS instruction (a
@@ -124,7 +130,7 @@ __shared__ uint32_t s_bnd_codes[kBndWaves][kRegion];
 __shared__ __align__(16) int32_t s_bnd_pos[kBndWaves][kRegion / 32 * kPosStride];
 // Segments of at most 65536 rows: positions as 16-bit values, biased by
 // 2^15 (pos - 32768 as a signed 16-bit number), 40 to a block of 32 entries
-// (80 bytes: the 16 blocks of a region start in 16 different bank groups),
+// (80 bytes: any 16 consecutive blocks start in 16 different bank groups),
 // each entry at element pos16_slot(j) of its block.
 constexpr int kPos16Stride = 40;
 __shared__ __align__(16) uint16_t s_bnd_pos16[kBndWaves][kRegion / 32 * kPos16Stride];
@@ -330,15 +336,27 @@ __global__ void __launch_bounds__(kBndWaves * 64)
       L.lim2 = b16 | (b16 << 16);
     }
     int2 res = make_int2(0, -1);
-    if (vmask != 0ull) {
-      // Stage the leader's list around the leader's insertion point.
-      const int leader = __ffsll((unsigned long long)vmask) - 1;
+    // Rounds: the first lane still waiting leads; the stretch of its list
+    // around its insertion point is staged, and every lane of that list whose
+    // insertion point lies far enough inside it is served from LDS.  A run of
+    // slots that crosses lists (levels, segments) or spreads over a sparse
+    // stretch takes a round per list or stretch.  When a round would serve
+    // fewer than a quarter of the lanes left (an order without locality), or the
+    // windows are too long for a stretch to hold, the rest join it: they search
+    // their lists in memory, all at once, and scan there what is not staged.
+    const bool fits = topk <= kMargin - kScanStep;
+    const int32_t reach = fits ? topk : 0;  // at least every second entry of a prefix list is in the pool
+    const int32_t before = fits ? reach + kScanStep : kMargin;
+    for (uint64_t pend = vmask; pend != 0ull;) {
+      bool go = valid && ((pend >> lane) & 1ull) != 0ull;
+      int32_t p = 0;
+      const int leader = __ffsll((unsigned long long)pend) - 1;
       const uint32_t* g_codes = readlane_ptr(Lq.codes, leader);
       const int32_t* g_pos = readlane_ptr(Lq.pos, leader);
       const int32_t g_n = __builtin_amdgcn_readlane(Lq.n, leader);
       const uint32_t g_key = uint32_t(__builtin_amdgcn_readlane(int32_t(key), leader));
       const int32_t p0 = wave_lower_bound(g_codes, 0, g_n, g_key, lane);
-      const int32_t r0 = (p0 - kMargin > 0 ? p0 - kMargin : 0) & ~(kScanStep - 1);
+      const int32_t r0 = (p0 - before > 0 ? p0 - before : 0) & ~(kScanStep - 1);
       const int32_t r1 = r0 + kRegion < g_n ? r0 + kRegion : g_n;
       {
         uint32_t cv[kRegion / 64];
@@ -361,14 +379,11 @@ __global__ void __launch_bounds__(kBndWaves * 64)
       }
       wave_lds_sync();
 
-      const bool staged = Lq.codes == g_codes;
-      L.r0 = staged ? r0 : 0;
-      L.r1 = staged ? r1 : 0;
-
-      // Lower bound of the code: in the staged range when it brackets the key.
-      int32_t p = 0;
-      bool found = false;
-      if (valid && staged && (r0 == 0 || s_bnd_codes[wave][0] < key) && (r1 == L.n || s_bnd_codes[wave][r1 - r0 - 1] >= key)) {
+      // Lower bound of the code in the staged stretch when it brackets the
+      // key; the leader's always does.
+      go = go && Lq.codes == g_codes && (r0 == 0 || s_bnd_codes[wave][0] < key) &&
+           (r1 == g_n || s_bnd_codes[wave][r1 - r0 - 1] >= key);
+      if (go) {
         int32_t lo = r0, hi = r1;
         while (lo < hi) {
           const int32_t mid = (lo + hi) >> 1;
@@ -378,20 +393,33 @@ __global__ void __launch_bounds__(kBndWaves * 64)
             hi = mid;
         }
         p = lo;
-        found = true;
+        go = lane == leader || ((r0 == 0 || p - r0 >= reach) && (r1 == g_n || r1 - p >= reach));
       }
-      // The rest search the list itself, one query at a time, wavefront-wide.
-      for (uint64_t m = wave_ballot(valid && !found); m != 0ull; m &= m - 1ull) {
-        const int u = __ffsll((unsigned long long)m) - 1;
-        const uint32_t* uc_p = readlane_ptr(L.codes, u);
-        const int32_t un = __builtin_amdgcn_readlane(L.n, u);
-        const uint32_t uk = uint32_t(__builtin_amdgcn_readlane(int32_t(key), u));
-        const int32_t up = wave_lower_bound(uc_p, 0, un, uk, lane);
-        if (lane == u) p = up;
+      const bool staged = Lq.codes == g_codes;
+      const uint64_t served = wave_ballot(go);
+      const uint64_t left = pend & ~served;
+      if (!fits || __popcll(served) * 4 < __popcll(left)) {
+        if (((left >> lane) & 1ull) != 0ull) {
+          int32_t lo = 0, hi = L.n;
+          while (lo < hi) {
+            const int32_t mid = (lo + hi) >> 1;
+            if (L.codes[mid] < key)
+              lo = mid + 1;
+            else
+              hi = mid;
+          }
+          p = lo;
+          go = true;
+        }
+        pend = 0ull;
+      } else {
+        pend = left;
       }
+      L.r0 = staged ? r0 : 0;
+      L.r1 = staged ? r1 : 0;
 
       // The window, entry by entry.
-      if (valid) {
+      if (go) {
         const int half = topk / 2;
         const int need_r = topk - half;
         // Right side: first and last entry taken; left side: nearest and
@@ -406,10 +434,10 @@ __global__ void __launch_bounds__(kBndWaves * 64)
           got_r = lane_scan<kPos16>(L, cur_r, +1, topk - got_l, got_r, r_first, r_last);
         if (got_l + got_r > 0) res = make_int2(got_l > 0 ? l_far : r_first, got_r > 0 ? r_last : l_near);
       }
-    }  // some lane has a pool
+      // Every read of the staged entries is done before they are replaced.
+      wave_lds_sync();
+    }
     if (slot < total) bounds[slot] = res;
-
-    wave_lds_sync();
   }
 }
 

@@ -475,6 +475,32 @@ def test_forward_zorder_matches_position_order():
     assert torch.equal(c.view(torch.int16), d.view(torch.int16))
 
 
+@pytest.mark.parametrize("N,topk,causal,chunk", [(65, 1, True, 0), (1000, 1, True, 0), (1000, 40, True, 0),
+                                                 (1000, 40, True, 93), (777, 16, False, 0), (3001, 1024, True, 0),
+                                                 (700, 128, True, 0)])
+def test_select_runs_over_several_lists(N, topk, causal, chunk):
+    """Runs of 64 slots that cross segments and list levels (N not a multiple
+    of 64; k = 1: a list per power of two), in the level-regrouped Z-order (a
+    staged stretch per list), in random and in position order (searched in
+    memory), and with clustered keys that leave most queries far from the
+    stretch of their neighbours."""
+    log(f"select over several lists N={N} k={topk} causal={causal} chunk={chunk}")
+    S = 3
+    rng = np.random.default_rng([N, topk])
+    qc = workloads.random_codes(N, (S, N), 12)
+    kc = workloads.random_codes(N + 1, (S, N), 12)
+    kc[1] = (kc[1] & 7) | (rng.integers(0, 4, N).astype(np.uint32) << 9)
+    want = oracle.select_topk(qc, kc, topk, causal, chunk=chunk)
+    esc, eperm = oracle.sort_keys(kc)
+    dq, dsc, dperm = u32_to_dev(qc), u32_to_dev(esc), i32_to_dev(eperm)
+    zorder = np.argsort(qc, axis=1, kind="stable").astype(np.int32)
+    shuffled = np.stack([rng.permutation(N) for _ in range(S)]).astype(np.int32)
+    regrouped = zeta.zeta_query_order(i32_to_dev(zorder), N, S, topk, causal, chunk=chunk)
+    for order in (regrouped, i32_to_dev(zorder), i32_to_dev(shuffled), None):
+        got = host(zeta.zeta_select_topk(dq, dsc, dperm, topk, causal, chunk=chunk, q_order=order))
+        assert np.array_equal(got, want)
+
+
 # ----------------------------------------------------------------------------
 # Query order by list level
 # ----------------------------------------------------------------------------

@@ -275,8 +275,8 @@ inline QueryOrderWs query_order_ws(int64_t S, int64_t N) {
 }
 
 // Gradients of the bfloat16 one-pass attention: the one-pass call's lists,
-// bounds and key rows, then per slot a 32-byte record, a copy of the dout row
-// and the deps part, each tile's window range per list and their envelopes,
+// bounds and key rows, then per slot a 32-byte record and the deps part, each
+// tile's window range per list and their envelopes,
 // each chunk's candidate tiles (in the envelopes' layout), the block sums of
 // deps and, with the history-mean candidate, the gradients reaching the means
 // and their scan's sums.
@@ -288,7 +288,7 @@ inline int tile_bwd_levels(int64_t N, int topk, bool causal) {
 }
 struct TileBwdWs {
   FusedWs fused;
-  size_t rec_off, dslot_off, part_off, env_off, env2_off, ranges_off, sums_off;
+  size_t rec_off, part_off, env_off, env2_off, ranges_off, sums_off;
   size_t hist_k_off, hist_v_off, hist_scan_off, bytes;
 };
 inline TileBwdWs tile_bwd_ws(int64_t S, int64_t N, int dv, int topk, int causal, bool history = false) {
@@ -298,8 +298,7 @@ inline TileBwdWs tile_bwd_ws(int64_t S, int64_t N, int dv, int topk, int causal,
   const size_t tiles = size_t(S) * size_t((N + 15) / 16);
   const size_t env = size_t(tile_bwd_levels(N, topk, causal != 0)) * tiles * 2 * sizeof(int32_t);
   w.rec_off = align_up(w.fused.bytes);
-  w.dslot_off = w.rec_off + align_up(rows * 32);
-  w.part_off = w.dslot_off + align_up(rows * size_t(dv) * 2);
+  w.part_off = w.rec_off + align_up(rows * 32);
   w.env_off = w.part_off + align_up(rows * sizeof(float));
   w.env2_off = w.env_off + align_up(env);
   w.ranges_off = w.env2_off + align_up(env);

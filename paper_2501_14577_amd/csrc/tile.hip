@@ -81,7 +81,6 @@ namespace zeta {
 namespace {
 
 constexpr int kTileQ = 16;     // queries per tile (product columns)
-constexpr int kChunk = 16;     // list entries per product step
 constexpr int kTileWaves = 4;  // wavefronts per block
 
 // Index-row tiles (the attend call given a processing order): the union of a
@@ -598,108 +597,6 @@ __global__ void __launch_bounds__(256)
 }
 
 // ---- attention over the windows ----------------------------------------------
-
-// Value rows reach the matrix cores through LDS.  Per chunk of 16 entries the
-// wavefront copies the 16 value rows straight from global memory into LDS
-// (global_load_lds_dwordx4: lane L's 16 bytes land at byte 16 L of the
-// instruction's 1 KiB), then reads each product's A operand with one
-// transposing LDS read (ds_read_b64_tr_b16: within each group of 16 lanes,
-// output lane i receives element i % 4 of the 8-byte reads of lanes
-// 4j + i / 4, j = 0..3).  With lane (g, s) of a group pointing at entry row
-// 4g + s / 4, columns 16 blk + 4 (s % 4) .. + 3, output lane i holds column
-// 16 blk + i of entries 4g .. 4g + 3: the A operand (value columns x
-// entries) of a 16 x 16 x 16 product, with no register shuffling (the kernel
-// repeats it in the upper K half of a 16 x 16 x 32 product, against the low
-// score parts).
-//
-// LDS row order.  One copy instruction fills R = 512 / d_v consecutive LDS
-// rows (P = d_v / 8 pieces of 16 bytes each).  For d_v <= 128 the lanes that
-// fill one LDS row share a tile-entry group kg, so each lane copies one of its
-// own 4 entries (whose position it already holds): LDS row
-// rho = j R + q (instruction j, q = lane / P) holds entry
-// 4 kg + j (16 / P) + q % (16 / P).  For d_v = 256 row rho holds entry rho.
-// Pieces are XOR-swizzled by row (sw below): physical piece p of row rho
-// holds logical piece p ^ sw(rho), so that the transposing reads are free of
-// bank conflicts.
-// Transposing LDS reads (ds_read_b64_tr_b16) at addr[j] + kOff, kCopies of
-// each (into a[kCopies j] .. a[kCopies j + kCopies - 1]), issued once the
-// copies into LDS made before the last kPending copy instructions have landed
-// (kPending -1: no wait here); read_tr_wait then waits for the results.
-// Written as inline assembly, with the waits, because the compiler would
-// otherwise wait for every copy still in flight (including the next chunk's,
-// which must keep loading meanwhile) before any such read.  LDS operations of
-// one wavefront complete in order, so the compiler's own waits on its later
-// LDS reads stay correct with these older ones in flight.
-template <int E, int kCopies, uint32_t kOff, int kPending>
-__device__ __forceinline__ void read_tr_issue(const uint32_t (&addr)[E], s16x4_t (&a)[E * kCopies]) {
-  static_assert(kPending >= -1 && kPending < 16, "vmcnt immediate (-1: no wait)");
-  if constexpr (kPending >= 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kPending) : "memory");
-#pragma unroll
-  for (int j = 0; j < E; ++j)
-#pragma unroll
-    for (int c = 0; c < kCopies; ++c)
-      asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2"
-                   : "=v"(a[kCopies * j + c])
-                   : "v"(addr[j]), "n"(kOff)
-                   : "memory");
-}
-
-// Waits for every LDS read of this wavefront; the reads' results are then
-// used only after the wait (each passes through an ordered empty statement).
-template <int N>
-__device__ __forceinline__ void read_tr_wait(s16x4_t (&a)[N]) {
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0])::"memory");
-#pragma unroll
-  for (int j = 1; j < N; ++j) asm volatile("" : "+v"(a[j]));
-}
-
-template <int DV>
-struct VStage {
-  static constexpr int kRowBytes = 2 * DV;
-  static constexpr int kP = DV / 8;                   // 16-byte pieces per row
-  static constexpr int kR = 64 / kP;                  // LDS rows per copy instruction
-  static constexpr int kLoads = kChunk / kR;          // copy instructions per chunk
-  static constexpr int kOwn = kP <= 16 ? 16 / kP : 0; // rows of one entry group per instruction
-  static constexpr int kBlocks = DV / 16;             // products (16 value columns each) per chunk
-  static constexpr int kBytes = kChunk * kRowBytes;   // one chunk's rows
-  static_assert(kR >= 2 && kChunk % kR == 0, "d_v must be 32, 64, 128 or 256");
-  // Piece swizzle of LDS row rho.  A transposing read is served in two
-  // halves of 32 lanes (entry groups kg = 0, 1 and kg = 2, 3), each reading
-  // 256 bytes: the 16 (row, piece) pairs of one half must fall in 16
-  // different 16-byte bank groups.  Row rho's bank group is set by the row's
-  // offset within 256 bytes and the physical piece; the swizzle puts the
-  // row bits that the offset does not separate into the piece bits that the
-  // block index leaves free.
-  __device__ static constexpr int sw(int rho) {
-    if constexpr (kP == 16) {  // rho = 4u + kg: u into piece bits 2-3, kg's low bit into bit 1
-      return (rho & 12) | ((rho & 1) << 1);
-    } else if constexpr (kP == 8) {  // rho = 8(u >> 1) + 2kg + (u & 1)
-      return (((rho >> 1) & 1) << 1) | (((rho >> 3) & 1) << 2);
-    } else if constexpr (kP == 4) {  // rho = 4kg + u
-      return ((rho >> 2) & 1) << 1;
-    } else {  // kP == 32, rho = 4kg + u
-      return ((rho & 3) << 1) | (((rho >> 2) & 1) << 3);
-    }
-  }
-  // Chunk entry held by LDS row rho.
-  __device__ static constexpr int entry_of_row(int rho) {
-    if constexpr (kP > 16) {
-      return rho;
-    } else {
-      const int j = rho / kR, q = rho % kR;
-      return 4 * (q / kOwn) + j * kOwn + q % kOwn;
-    }
-  }
-  // LDS row holding chunk entry e.
-  __device__ static constexpr int row_of_entry(int e) {
-    if constexpr (kP > 16) {
-      return e;
-    } else {
-      const int kg = e / 4, u = e % 4;
-      return (u / kOwn) * kR + kg * kOwn + u % kOwn;
-    }
-  }
-};
 
 // kIdx: the windows are index rows (idx, topk <= kIdxTileMaxTopk, d_k = 3)
 // instead of list ranges; `order` is then required and the list arguments

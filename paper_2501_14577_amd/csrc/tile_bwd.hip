@@ -15,16 +15,15 @@
 //       U = sum S^2 p (q - k), R = sum S^2 (q - k),
 //     so one walk gives c = P / Z, dq = -(2 / Z)(U - c R) and the query's
 //     part of deps, -(X - c Y) / Z.  Per slot it stores a 32-byte record (q,
-//     list, 1/Z, c, window bounds, pool limit) and the query's dout row, so
-//     that a tile's data is contiguous for the key pass; per list it stores
-//     the first and last list index of the tile's windows.
+//     list, 1/Z, c, window, pool limit, position) for the key pass; per list
+//     it stores the first and last list index of the tile's windows.
 //  2. Envelopes, per segment and level: the running maximum (from the first
 //     tile) of the tiles' last indices and the running minimum (from the last
 //     tile) of their first indices.  Both are non-decreasing, so the tiles
 //     whose windows meet a chunk lie between two positions, found by binary
 //     search per chunk.
 //  3. Key pass, one launch per list (the full sorted list first, then each
-//     prefix list), one wavefront per 16-entry chunk.  Over the candidate
+//     prefix list), one wavefront per two 16-entry chunks.  Over the candidate
 //     tiles (64 tiles' ranges tested at once) a lane takes one entry and 4 of
 //     the tile's queries: S_ij, the dot
 //     products (dout x V^T, one product per 32 columns), w_ij and A_ij.  dv^T
@@ -50,25 +49,27 @@
 #include "select_device.h"
 #include "tile_device.h"
 
+#include <type_traits>
+
 namespace zeta {
 namespace {
 
 constexpr int kBtWaves = 4;          // wavefronts per block
-constexpr int kBtStage = 512;        // list entries staged at once by the query pass
-constexpr int kBtChunk = 16;         // list entries per product step
-constexpr int kBtStageChunks = kBtStage / kBtChunk;
+constexpr int kBtChunk = kChunk;      // list entries per product step
 constexpr int kRedThreads = 256;
 constexpr uint32_t kNoList = 0xFFFFu;  // record of a slot whose query has no window
 
 // What the key pass needs of a slot's query, in 32 bytes: q as bfloat16 bits,
-// the list index (kNoList: no window), 1/Z, c, the window's list-index bounds
-// and the pool limit.
+// the list index (kNoList: no window), 1/Z, c, the window as its first list
+// index a and its last less a (no window: a = INT32_MIN, span = 0, which no
+// entry meets), the pool limit and the query's position.
 struct alignas(16) SlotRec {
   uint32_t q01;     // q[0] | q[1] << 16
   uint32_t q2_list;  // q[2] | list index << 16
   float zinv, c;
-  int32_t a, b;
-  uint32_t lim, pad;
+  int32_t a;
+  uint32_t span, lim;
+  int32_t row;
 };
 
 // The list of a level: the full sorted list, or prefix list `lvl`.
@@ -135,7 +136,13 @@ __device__ __forceinline__ int level_index(int lvl, int causal, int t0, int t_hi
 }
 
 // ---- 1. query pass ----------------------------------------------------------
-template <int DV, bool kHist>
+// Bound: vector issue (about 130 instructions per chunk: distances, tests, the
+// ten sums), with the value rows' latency behind it.  The rows are copied
+// straight into LDS a chunk ahead, as in the forward, instead of gathered into
+// registers, and no copy of the dout rows is kept for the key pass (it gathers
+// them itself).  16 x 65536, k 128, d_v 128: 616 -> 400 us; 96 x 8192, k 64, d_v
+// 64: 207 -> 153 us.
+template <int DV, bool kOff32, bool kHist>
 __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per_eu(DV <= 128 ? 3 : 1)))
     bwd_tile_query_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ v,
                           const uint16_t* __restrict__ dout, const int32_t* __restrict__ sorted_pos,
@@ -143,20 +150,48 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
                           const int2* __restrict__ bounds, const uint2* __restrict__ keys_full,
                           const uint2* __restrict__ keys_list, int64_t S, int64_t N, int64_t ct, int causal,
                           int chunk, int t0, int t_hi, int levels, int64_t cap, float eps, float* __restrict__ dq,
-                          SlotRec* __restrict__ rec, uint16_t* __restrict__ dslot, float* __restrict__ deps_part,
+                          SlotRec* __restrict__ rec, float* __restrict__ deps_part,
                           int2* __restrict__ env, const float* __restrict__ mk, const float* __restrict__ mv,
                           float* __restrict__ hk, float* __restrict__ hv) {
   constexpr int NS = DV / 32;  // 32-column slices of a row: one product each
   static_assert(DV % 32 == 0, "d_v must be a multiple of 32");
-  __shared__ __align__(16) int32_t s_pos[kBtWaves][kBtStage];
-  __shared__ __align__(16) float s_k[kBtWaves][kBtStage][4];
+  using VS = VStage<DV>;
+  using Off = typename RowOff<kOff32>::type;
+  // List entries staged at once (x, y, z, position), and two chunks of value
+  // rows copied straight into LDS (even chunks, odd chunks).
+  constexpr int kBtStage = DV <= 128 ? 320 : 128;
+  constexpr int kBtStageChunks = kBtStage / kBtChunk;
+  static_assert(kBtStage % 64 == 0, "staging fills rounds of 64 entries");
+  __shared__ __align__(16) float s_ent[kBtWaves][kBtStage][4];
+  __shared__ __align__(16) unsigned char s_v[kBtWaves][2 * VS::kBytes];
 
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  // Wave-uniform (the LDS destination of a copy instruction must be).
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
   const int qn = lane & 15;  // this lane's query (B column) and entry (A row)
   const int kg = lane >> 4;  // this lane's entries 4kg..4kg+3 and column slice 8kg..8kg+7
   const int64_t tiles = S * ct;
   const int64_t nb = gridDim.x;
+
+  // Copy instruction j: this lane's piece of the value row of chunk entry
+  // entry_of_row(j kR + vq); the row fragments it reads back (entry qn, columns
+  // 32s + 8kg .. + 7) lie at row_addr[s] of the even buffer.
+  const int vq = lane / VS::kP, vp = lane % VS::kP;
+  uint32_t copy_off[VS::kLoads];
+  int copy_ent[VS::kLoads];
+#pragma unroll
+  for (int j = 0; j < VS::kLoads; ++j) {
+    copy_off[j] = uint32_t(16 * (vp ^ VS::sw(j * VS::kR + vq)));
+    copy_ent[j] = VS::entry_of_row(j * VS::kR + vq);
+  }
+  uint32_t row_addr[NS];
+  {
+    const int rho = VS::row_of_entry(qn);
+    const uint32_t base = uint32_t(reinterpret_cast<uintptr_t>(
+        (const __attribute__((address_space(3))) unsigned char*)(&s_v[wave][0])));
+#pragma unroll
+    for (int s = 0; s < NS; ++s) row_addr[s] = base + uint32_t(rho * VS::kRowBytes + 16 * ((4 * s + kg) ^ VS::sw(rho)));
+  }
 
   for (int64_t blk = xcd_contiguous_block(blockIdx.x, nb); blk * kBtWaves < tiles; blk += nb) {
     const int64_t tile = blk * kBtWaves + wave;
@@ -177,18 +212,13 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
         my_b = bb.y;
       }
     }
-    // Slots without a query still hold a defined record, deps part and (zero)
-    // dout row.
-    if (xs < N && my_i < 0) {
-      if (kg == 0) {
-        SlotRec r = {};
-        r.q2_list = kNoList << 16;
-        rec[slot] = r;
-        deps_part[slot] = 0.0f;
-      }
-#pragma unroll
-      for (int s2 = 0; s2 < NS; ++s2)
-        *reinterpret_cast<uint4*>(dslot + slot * DV + 32 * s2 + 8 * kg) = make_uint4(0u, 0u, 0u, 0u);
+    // Slots without a query still hold a defined record and deps part.
+    if (xs < N && my_i < 0 && kg == 0) {
+      SlotRec r = {};
+      r.q2_list = kNoList << 16;
+      r.a = INT32_MIN;
+      rec[slot] = r;
+      deps_part[slot] = 0.0f;
     }
     uint32_t pending = uint32_t(wave_ballot(my_i >= 0)) & 0xFFFFu;
 
@@ -221,13 +251,6 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
 #pragma unroll
         for (int s = 0; s < NS; ++s) load8(dout + gq * DV + 32 * s + 8 * kg, dfr[s]);
       }
-      // The slot's copy of its dout row (zeros without a window).
-      if (in_grp) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-          *reinterpret_cast<uint4*>(dslot + slot * DV + 32 * s + 8 * kg) =
-              make_uint4(dfr[s][0], dfr[s][1], dfr[s][2], dfr[s][3]);
-      }
       float z = 0.0f, pz = 0.0f, xz = 0.0f, yz = 0.0f;
       float u[3] = {0.0f, 0.0f, 0.0f}, rr[3] = {0.0f, 0.0f, 0.0f};
 
@@ -235,31 +258,33 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
       const uint32_t span = mine ? uint32_t(my_b - my_a) : 0u;
       const int32_t a_eff = mine ? my_a : INT32_MIN;
       const uint32_t lim_u = uint32_t(my_lim);
-      const uint16_t* vseg = v + seg * N * DV;
+      const unsigned char* vbytes = reinterpret_cast<const unsigned char*>(v + seg * N * DV);
 
-      // Value slices of entry qn of staged chunk ch (row 0 for a chunk past
-      // the burst: loaded, never used).
-      auto load_v = [&](int ch, int nch_, uint32_t(&vf)[NS][4]) {
-        const int chc = ch < nch_ ? ch : 0;
-        const int32_t pv = s_pos[wave][chc * kBtChunk + qn];
+      // Copy the value rows of staged chunk ch into LDS buffer `buf` (a missing
+      // entry reads row 0 and has weight 0).
+      auto copy_rows = [&](int ch, unsigned char* buf) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) load8(vseg + int64_t(pv) * DV + 32 * s + 8 * kg, vf[s]);
+        for (int j = 0; j < VS::kLoads; ++j) {
+          const int32_t pv = __float_as_int(s_ent[wave][ch * kBtChunk + copy_ent[j]][3]);
+          const Off boff = Off(pv) * Off(VS::kRowBytes) + Off(copy_off[j]);
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(vbytes + boff),
+                                           (__attribute__((address_space(3))) void*)(buf + 1024 * j), 16, 0, 0);
+        }
       };
-      // Sums over this lane's 4 entries of chunk ch.
-      auto accumulate = [&](int cb, int ch, const uint32_t(&vf)[NS][4]) {
+      // Sums over this lane's 4 entries of chunk ch, whose rows' fragments are vf.
+      auto accumulate = [&](int cb, int ch, const u32x4_t(&vf)[NS]) {
         f32x4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int s = 0; s < NS; ++s) d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag8(vf[s]).v, frag8(dfr[s]).v, d, 0, 0, 0);
-        const int4 p4 = *reinterpret_cast<const int4*>(&s_pos[wave][ch * kBtChunk + kg * 4]);
-        const int32_t pvs[4] = {p4.x, p4.y, p4.z, p4.w};
+        for (int s = 0; s < NS; ++s)
+          d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vf[s]), frag8(dfr[s]).v, d, 0, 0, 0);
         const int32_t r0 = (cb + ch) * kBtChunk + kg * 4;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-          const float4 kr = *reinterpret_cast<const float4*>(&s_k[wave][ch * kBtChunk + kg * 4 + kk][0]);
+          const float4 kr = *reinterpret_cast<const float4*>(&s_ent[wave][ch * kBtChunk + kg * 4 + kk][0]);
           const float df[3] = {qv[0] - kr.x, qv[1] - kr.y, qv[2] - kr.z};
-          const float d2 = fmaf(df[2], df[2], fmaf(df[1], df[1], df[0] * df[0]));
-          const bool in = uint32_t(r0 + kk) - uint32_t(a_eff) <= span && uint32_t(pvs[kk]) <= lim_u;
-          const float sc = in ? __builtin_amdgcn_rcpf(d2 + eps) : 0.0f;
+          const float d2 = fmaf(df[2], df[2], fmaf(df[1], df[1], fmaf(df[0], df[0], eps)));
+          const bool in = uint32_t(r0 + kk) - uint32_t(a_eff) <= span && uint32_t(__float_as_int(kr.w)) <= lim_u;
+          const float sc = in ? __builtin_amdgcn_rcpf(d2) : 0.0f;
           const float p = d[kk];
           const float s2 = sc * sc;
           z += sc;
@@ -308,22 +333,29 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
               if (e_ < nch * kBtChunk) {
                 float kv[3];
                 key_row(kw[t], kv);
-                s_pos[wave][e_] = pv[t];
-                *reinterpret_cast<float4*>(&s_k[wave][e_][0]) = make_float4(kv[0], kv[1], kv[2], 0.0f);
+                *reinterpret_cast<float4*>(&s_ent[wave][e_][0]) = make_float4(kv[0], kv[1], kv[2], __int_as_float(pv[t]));
               }
             }
           }
           wave_lds_sync();
-          // Value slices of chunk ch+1 load while chunk ch is summed.
-          uint32_t vA[NS][4], vB[NS][4];
-          load_v(0, nch, vA);
+          // Chunk ch+1's value rows are copied while chunk ch is summed (past
+          // the last chunk the other buffer receives that chunk again, so that
+          // one chunk's copies are always in flight behind the one being read).
+          unsigned char* const v0 = s_v[wave];
+          unsigned char* const v1 = s_v[wave] + VS::kBytes;
+          u32x4_t vf[NS];
+          copy_rows(0, v0);
           for (int ch = 0; ch < nch; ch += 2) {
-            load_v(ch + 1, nch, vB);
-            accumulate(cb, ch, vA);
+            copy_rows(ch + 1 < nch ? ch + 1 : ch, v1);
+            read_rows16<0, VS::kLoads>(row_addr, vf);
+            accumulate(cb, ch, vf);
             if (ch + 1 >= nch) break;
-            load_v(ch + 2, nch, vA);
-            accumulate(cb, ch + 1, vB);
+            copy_rows(ch + 2 < nch ? ch + 2 : ch + 1, v0);
+            read_rows16<VS::kBytes, VS::kLoads>(row_addr, vf);
+            accumulate(cb, ch + 1, vf);
           }
+          // Every copy has landed before the buffers are refilled.
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           wave_lds_sync();
         }
         c = wave_min_int(a_ch > e ? a_ch : INT32_MAX);
@@ -359,7 +391,7 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
           p_m = kg_sum(part);
 #pragma unroll
           for (int a = 0; a < 3; ++a) dm[a] = qv[a] - mk[gq * 3 + a];
-          s_m = __builtin_amdgcn_rcpf(fmaf(dm[2], dm[2], fmaf(dm[1], dm[1], dm[0] * dm[0])) + eps);
+          s_m = __builtin_amdgcn_rcpf(fmaf(dm[2], dm[2], fmaf(dm[1], dm[1], fmaf(dm[0], dm[0], eps))));
           const float s2 = s_m * s_m;
           z += s_m;
           pz = fmaf(s_m, p_m, pz);
@@ -409,10 +441,10 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
         r.q2_list = (__float_as_uint(qv[2]) >> 16) | (list << 16);
         r.zinv = inv;
         r.c = cc;
-        r.a = my_a;
-        r.b = my_b;
-        r.lim = uint32_t(my_lim);
-        r.pad = 0u;
+        r.a = mine ? my_a : INT32_MIN;
+        r.span = span;
+        r.lim = lim_u;
+        r.row = my_i;
         rec[slot] = r;
       }
     }
@@ -505,262 +537,294 @@ __global__ void __launch_bounds__(256)
 }
 
 // ---- 3. key pass ------------------------------------------------------------------
-// A block's wavefronts take consecutive chunks of one list and segment and
-// walk the union of their candidate tiles together.  Each tile's 16 records
-// and 16 dout rows are staged once in LDS for all of them (two buffers: the next
-// tile's bytes load while the current tile is summed, one barrier per tile);
-// a wavefront skips the tiles its own chunk does not meet.  Dout rows are
-// padded by 16 bytes, so that lanes reading 16 different rows use different
-// banks.
-constexpr int kKeyWaves = 4;  // chunks per block (one per wavefront)
+// A wavefront takes kKeySub consecutive 16-entry chunks of one list (two, one
+// for d_v = 256, whose sums fill the registers) and walks the tiles whose
+// windows meet them, so that a tile's dout rows, copied into LDS, serve both
+// chunks.  Wavefronts share nothing, so no barrier holds the fast ones up: while
+// a tile is summed the next tile's rows are copied straight into LDS and the
+// records of the one after it load into registers.  The rows are read back
+// twice: as they lie (dot products, A operand: the tile's queries x 32 columns)
+// and transposed (dv, A operand: 16 columns x queries).
+// Two chunks, not one: the dout rows, their two reads and the records are then
+// shared, and the longer visits outweigh the third wavefront per SIMD that one
+// chunk leaves room for (16 x 65536, k 128, d_v 128: 886 against 935 us; with the
+// barrier-coupled blocks of four chunks before, 1144 us; 96 x 8192, k 64, d_v 64:
+// 340 against 355, before 431 us).  A wavefront spends about a quarter of its time
+// on its first dependent loads and a third on the sums; the prefix lists' adds
+// (dv read and written again) take a quarter of the call.  Persistent wavefronts
+// that prefetch the next unit were slower (1004 us: they wait for their own
+// stores).
+constexpr int kKeyWaves = 4;  // wavefronts per block
 constexpr int kKeyThreads = kKeyWaves * 64;
+template <int DV>
+constexpr int kKeySub = DV <= 128 ? 2 : 1;  // chunks per wavefront
 
 template <int DV, bool kOff32>
-__global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_eu(DV <= 128 ? 3 : 2)))
-    bwd_tile_key_kernel(const uint16_t* __restrict__ v, const int32_t* __restrict__ sorted_pos,
-                        const int32_t* __restrict__ list_pos, const uint2* __restrict__ keys_full,
-                        const uint2* __restrict__ keys_list, const SlotRec* __restrict__ rec,
-                        const uint16_t* __restrict__ dslot, const int2* __restrict__ env,
+__global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_eu(DV <= 64 ? 3 : 2)))
+    bwd_tile_key_kernel(const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
+                        const int32_t* __restrict__ sorted_pos, const int32_t* __restrict__ list_pos,
+                        const uint2* __restrict__ keys_full, const uint2* __restrict__ keys_list,
+                        const SlotRec* __restrict__ rec, const int2* __restrict__ env,
                         const int2* __restrict__ ranges, int64_t S, int64_t N, int64_t ct, int causal, int t0,
                         int t_hi, int levels, int64_t cap, int lvl, int first, float eps, float* __restrict__ dk,
                         float* __restrict__ dv) {
+  using VS = VStage<DV>;
   constexpr int NS = DV / 32;
-  constexpr int E = DV / 16;  // value elements per lane and row in the dv product
-  constexpr int W = E / 2;
-  constexpr int kRowU = DV / 8;                                   // 16-byte units per dout row
-  constexpr int kDoutU = 16 * kRowU;                              // units of a tile's dout rows
-  constexpr int kStU = (kDoutU + kKeyThreads - 1) / kKeyThreads;  // dout units staged per thread
-  // Byte offsets into a segment's records and dout rows: 32-bit when the
-  // segment's dout rows span under 4 GiB.
+  constexpr int E = VS::kBlocks;  // 16-column blocks of a row: one dv product each
+  constexpr int SUB = kKeySub<DV>;
+  // Byte offsets into a segment's dout rows: 32-bit when they span under 4 GiB.
   using Off = typename RowOff<kOff32>::type;
-  __shared__ __align__(16) uint32_t s_rec[2][16][8];
-  __shared__ __align__(16) uint16_t s_dout[2][16][DV + 8];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int ent = lane & 15;  // this lane's entry (B column, and A row of the dot products)
+  __shared__ __align__(16) uint32_t s_rec[kKeyWaves][2][16][8];
+  __shared__ __align__(512) unsigned char s_d[kKeyWaves][2 * VS::kBytes];
+  const int lane = threadIdx.x & 63;
+  // Wave-uniform (the LDS destination of a copy instruction must be).
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int ent = lane & 15;  // this lane's entry of each chunk (B column)
   const int kg = lane >> 4;   // this lane's queries 4kg..4kg+3 of a tile
   const uint32_t li = uint32_t(level_index(lvl, causal, t0, t_hi, levels));
   const int64_t ln = (causal && lvl <= t_hi) ? (int64_t(1) << lvl) : N;
-  const int64_t cl = (ln + kBtChunk - 1) / kBtChunk;
-  const int64_t gps = (cl + kKeyWaves - 1) / kKeyWaves;  // groups of 4 chunks per segment
-  const int64_t groups = S * gps;
+  const int64_t cl = (ln + kBtChunk - 1) / kBtChunk;  // chunks per segment
+  const int64_t cw = (cl + SUB - 1) / SUB;            // wavefronts' worth of them
+  const int64_t total = S * cw;
   const int64_t nb = gridDim.x;
   const int32_t n32 = int32_t(N);
 
-  for (int64_t blk = xcd_contiguous_block(blockIdx.x, nb); blk < groups; blk += nb) {
-    const int64_t seg = blk / gps;
-    const int64_t c0 = (blk - seg * gps) * kKeyWaves;
-    const int64_t c_last = (c0 + kKeyWaves < cl ? c0 + kKeyWaves : cl) - 1;
-    const int64_t c = c0 + wave;
-    const bool live = c < cl;
+  // Copy instruction j: this lane's piece of the dout row of tile query
+  // entry_of_row(j kR + vq), whose position lane copy_src + j copy_step holds;
+  // row fragments (query ent) and transposed fragments of a buffer (see VStage).
+  const int vq = lane / VS::kP, vp = lane % VS::kP;
+  uint32_t copy_off[VS::kLoads];
+#pragma unroll
+  for (int j = 0; j < VS::kLoads; ++j) copy_off[j] = uint32_t(16 * (vp ^ VS::sw(j * VS::kR + vq)));
+  const int copy_src = 2 * VS::entry_of_row(vq) + 1;
+  constexpr int copy_step = 2 * (VS::entry_of_row(VS::kR % kChunk) - VS::entry_of_row(0));
+  uint32_t row_off[NS], tr_off[E];
+  {
+    const int rho = VS::row_of_entry(ent);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) row_off[s] = uint32_t(rho * VS::kRowBytes + 16 * ((4 * s + kg) ^ VS::sw(rho)));
+    const int rt = VS::row_of_entry(4 * kg + ent / 4);
+    const int x = (ent % 4) / 2, half = ent % 2;
+#pragma unroll
+    for (int j = 0; j < E; ++j) tr_off[j] = uint32_t(rt * VS::kRowBytes + 16 * ((2 * j + x) ^ VS::sw(rt)) + 8 * half);
+  }
+
+  for (int64_t blk = xcd_contiguous_block(blockIdx.x, nb); blk * kKeyWaves < total; blk += nb) {
+    const int64_t unit = blk * kKeyWaves + wave;
+    if (unit >= total) continue;
+    const int64_t seg = unit / cw;
+    const int64_t c = (unit - seg * cw) * SUB;  // this wavefront's first chunk
     const LevelList L = level_list(sorted_pos, list_pos, keys_full, keys_list, seg, N, causal, lvl, t0, t_hi, cap);
-    const int32_t e = int32_t(c * kBtChunk + ent);
-    const bool valid_e = live && e < L.n;
-    const int32_t pos_e = valid_e ? L.pos[e] : 0;
-    float kv[3] = {0.0f, 0.0f, 0.0f};
-    if (valid_e) key_row(L.key[e], kv);
     const uint16_t* vseg = v + seg * N * DV;
-    uint32_t vfr[NS][4];  // value slices of this lane's entry: columns 32s + 8kg .. + 7
+    int32_t e[SUB], pos_e[SUB];
+    float kv[SUB][3];
+    uint32_t vfr[SUB][NS][4];  // value slices of this lane's entries: columns 32s + 8kg .. + 7
 #pragma unroll
-    for (int s = 0; s < NS; ++s) load8(vseg + int64_t(pos_e) * DV + 32 * s + 8 * kg, vfr[s]);
-
-    f32x4_t acc[E];
+    for (int u = 0; u < SUB; ++u) {
+      // An entry past the list's end lies outside every window.
+      e[u] = int32_t((c + u) * kBtChunk + ent);
+      pos_e[u] = e[u] < L.n ? L.pos[e[u]] : 0;
+      const uint2 kw = e[u] < L.n ? L.key[e[u]] : make_uint2(0u, 0u);
+      key_row(kw, kv[u]);
+    }
 #pragma unroll
-    for (int j = 0; j < E; ++j) acc[j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    float gk[3] = {0.0f, 0.0f, 0.0f};
-    bool touched = false;
+    for (int u = 0; u < SUB; ++u) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) load8(vseg + int64_t(pos_e[u]) * DV + 32 * s + 8 * kg, vfr[u][s]);
+    }
 
-    // This wave's chunk (empty when past the list) and the group's entries.
-    const int lo_c = live ? int(c * kBtChunk) : 1;
-    const int hi_c = live ? int(c * kBtChunk + kBtChunk - 1 < ln - 1 ? c * kBtChunk + kBtChunk - 1 : ln - 1) : 0;
-    const int lo_g = int(c0 * kBtChunk);
-    const int hi_g = int(c_last * kBtChunk + kBtChunk - 1 < ln - 1 ? c_last * kBtChunk + kBtChunk - 1 : ln - 1);
+    f32x4_t acc[SUB][E];
+    float gk[SUB][3];
+#pragma unroll
+    for (int u = 0; u < SUB; ++u) {
+#pragma unroll
+      for (int j = 0; j < E; ++j) acc[u][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int a = 0; a < 3; ++a) gk[u][a] = 0.0f;
+    }
+
+    const int lo_c = int(c * kBtChunk);
+    const int hi_c = int((c + SUB) * kBtChunk < ln ? (c + SUB) * kBtChunk : ln) - 1;
     const int2* ev = env + (int64_t(li) * S + seg) * ct;
     const int2* rgs = ranges + (int64_t(li) * S + seg) * ct;
-    // The candidate ranges grow with the chunk: the group's is from its first
-    // chunk's start to its last chunk's end.
-    const int64_t ta = rgs[c0].x, tb = rgs[c_last].y;
-    const unsigned char* rbase = reinterpret_cast<const unsigned char*>(rec + seg * N);
-    const unsigned char* dbase = reinterpret_cast<const unsigned char*>(dslot + seg * N * DV);
+    // The candidate ranges grow with the chunk.
+    const int64_t ta = rgs[c].x, tb = rgs[c + SUB - 1 < cl ? c + SUB - 1 : cl - 1].y;
+    const SlotRec* rseg = rec + seg * N;
+    const unsigned char* dbytes = reinterpret_cast<const unsigned char*>(dout + seg * N * DV);
 
-    // The tiles whose windows meet the group, 64 candidates tested at once
-    // (the same in every wavefront); with each, whether it meets this wave's
-    // chunk.
+    // The tiles whose windows meet the chunks, 64 candidates tested at once.
     int64_t blk_base = ta, cur_base = ta;
-    uint64_t pend = 0ull, mine = 0ull;
-    auto next_tile = [&](bool& hit_w) -> int64_t {
+    uint64_t pend = 0ull;
+    auto next_tile = [&]() -> int32_t {
       while (pend == 0ull && blk_base < tb) {
         const int64_t tl = blk_base + lane;
-        bool hg = false, hw = false;
+        bool hit = false;
         if (tl < tb) {
           const int2 rg = ev[tl];
-          hg = (rg.x <= hi_g) & (rg.y >= lo_g);
-          hw = (rg.x <= hi_c) & (rg.y >= lo_c);
+          hit = (rg.x <= hi_c) & (rg.y >= lo_c);
         }
-        pend = wave_ballot(hg);
-        mine = wave_ballot(hw);
+        pend = wave_ballot(hit);
         cur_base = blk_base;
         blk_base += 64;
       }
       if (pend == 0ull) return -1;
       const int b = __ffsll((unsigned long long)pend) - 1;
       pend &= pend - 1ull;
-      hit_w = ((mine >> b) & 1ull) != 0ull;
-      return cur_base + b;
+      return int32_t(cur_base) + b;
     };
-    uint4 st_rec = make_uint4(0u, 0u, 0u, 0u);  // 16 bytes of the records (threads 0..31)
-    uint4 st_dout[kStU];
-    auto stage = [&](int64_t tau) {
-      const int32_t t16 = int32_t(tau) * 16;
-      if (tid < 32) {
-        const int32_t xs = t16 + (tid >> 1);
-        const Off xq = Off(xs < n32 ? xs : n32 - 1);
-        st_rec = *reinterpret_cast<const uint4*>(rbase + xq * Off(sizeof(SlotRec)) + Off((tid & 1) * 16));
+    // Half a record per lane (lanes 0..31; the others repeat them): q, list,
+    // 1/Z, c on even lanes, window, pool limit and position on odd ones.  (The
+    // slots past the segment's end of its last tile read what follows its
+    // records in the workspace; their records are replaced before use.)
+    uint4 st = make_uint4(0u, 0u, 0u, 0u);
+    auto load_rec = [&](int32_t tau) { st = reinterpret_cast<const uint4*>(rseg + tau * 16)[lane & 31]; };
+    // The loaded records into buffer `buf` (a query of another list, or past
+    // the segment's end, gets the empty window and position 0), and their dout
+    // rows' copies issued (weight 0 where the window is empty).
+    auto stage = [&](int32_t tau, int buf) {
+      const uint32_t list = uint32_t(__builtin_amdgcn_update_dpp(int(st.y), int(st.y), 0xB1, 0xF, 0xF, false)) >> 16;  // the pair's other lane
+      const bool past = tau * 16 + ((lane & 31) >> 1) >= n32;
+      if (past) st = make_uint4(0u, 0u, 0u, 0u);
+      if ((lane & 1) != 0 && (past || list != li)) {
+        st.x = uint32_t(INT32_MIN);
+        st.y = 0u;
+        st.w = 0u;
       }
+      if (lane < 32) *reinterpret_cast<uint4*>(&s_rec[wave][buf][lane >> 1][(lane & 1) * 4]) = st;
 #pragma unroll
-      for (int u = 0; u < kStU; ++u) {
-        const int unit = u * kKeyThreads + tid;
-        if (unit < kDoutU) {
-          const int32_t xs = t16 + unit / kRowU;
-          const Off xq = Off(xs < n32 ? xs : n32 - 1);
-          st_dout[u] = *reinterpret_cast<const uint4*>(dbase + (xq * Off(DV) + Off((unit % kRowU) * 8)) * Off(2));
-        }
+      for (int j = 0; j < VS::kLoads; ++j) {
+        const int32_t row = __shfl(int(st.w), copy_src + j * copy_step, 64);
+        const Off boff = Off(row) * Off(VS::kRowBytes) + Off(copy_off[j]);
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(dbytes + boff),
+                                         (__attribute__((address_space(3))) void*)(s_d[wave] + buf * VS::kBytes + 1024 * j),
+                                         16, 0, 0);
       }
     };
-    auto store = [&](int buf) {
-      if (tid < 32) *reinterpret_cast<uint4*>(&s_rec[buf][tid >> 1][(tid & 1) * 4]) = st_rec;
+    // The rows' fragments of buffer `buf`, as they lie and transposed (read
+    // twice, once per K half of the products).
+    u32x4_t dr[NS];
+    s16x4_t tr[2 * E];
+    auto read_tile = [&](int buf) {
+      const unsigned char* rows = s_d[wave] + buf * VS::kBytes;
 #pragma unroll
-      for (int u = 0; u < kStU; ++u) {
-        const int unit = u * kKeyThreads + tid;
-        if (unit < kDoutU) *reinterpret_cast<uint4*>(&s_dout[buf][unit / kRowU][(unit % kRowU) * 8]) = st_dout[u];
-      }
-    };
-    auto sum_tile = [&](int64_t tau, int buf) {
-      SlotRec rq[4];  // records of the tile's queries 4kg..4kg+3
-#pragma unroll
-      for (int r = 0; r < 4; ++r) rq[r] = *reinterpret_cast<const SlotRec*>(&s_rec[buf][kg * 4 + r][0]);
-      // Dot products: lane holds p for queries 4kg..4kg+3 and entry ent (A
-      // rows: dout of the tile's query ent).
-      f32x4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const uint4 x = *reinterpret_cast<const uint4*>(&s_dout[buf][ent][32 * s + 8 * kg]);
-        const uint32_t dw[4] = {x.x, x.y, x.z, x.w};
-        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag8(dw).v, frag8(vfr[s]).v, d, 0, 0, 0);
-      }
-      float aw[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const SlotRec& rr = rq[r];
-        const float qx = __uint_as_float(rr.q01 << 16);
-        const float qy = __uint_as_float(rr.q01 & 0xFFFF0000u);
-        const float qz = __uint_as_float(rr.q2_list << 16);
-        const float df[3] = {qx - kv[0], qy - kv[1], qz - kv[2]};
-        const float d2 = fmaf(df[2], df[2], fmaf(df[1], df[1], df[0] * df[0]));
-        const bool in = ((rr.q2_list >> 16) == li) & (int32_t(tau) * 16 + kg * 4 + r < n32) & valid_e &
-                        (uint32_t(e - rr.a) <= uint32_t(rr.b - rr.a)) & (uint32_t(pos_e) <= rr.lim);
-        const float sc = in ? __builtin_amdgcn_rcpf(d2 + eps) : 0.0f;
-        aw[r] = sc * rr.zinv;
-        const float w = (d[r] - rr.c) * sc * aw[r];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) gk[a] = fmaf(w, df[a], gk[a]);
-      }
-      // dv^T += dout^T (columns x queries) * A (queries x entries), high and
-      // low parts of A in one product per 16 columns; A rows from the dout
-      // rows of queries 4kg..4kg+3, elements ent*E .. ent*E + E - 1.
-      Frag8 b;
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const bf16x2_t h = {(__bf16)aw[2 * t], (__bf16)aw[2 * t + 1]};
-        const uint32_t hw = __builtin_bit_cast(uint32_t, h);
-        const bf16x2_t l = {(__bf16)(aw[2 * t] - __uint_as_float(hw << 16)),
-                            (__bf16)(aw[2 * t + 1] - __uint_as_float(hw & 0xFFFF0000u))};
-        b.w[t] = hw;
-        b.w[t + 2] = __builtin_bit_cast(uint32_t, l);
-      }
-      uint32_t raw[4][W];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) load_words<W>(&s_dout[buf][kg * 4 + r][ent * E], raw[r]);
+      for (int s = 0; s < NS; ++s) dr[s] = *reinterpret_cast<const u32x4_t*>(rows + row_off[s]);
 #pragma unroll
       for (int j = 0; j < E; ++j) {
-        Frag8 a;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const uint32_t x = raw[2 * t][j >> 1], y = raw[2 * t + 1][j >> 1];
-          a.w[t] = __builtin_amdgcn_perm(y, x, (j & 1) ? 0x07060302u : 0x05040100u);
-          a.w[t + 2] = a.w[t];
-        }
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, acc[j], 0, 0, 0);
+        auto* at = (__attribute__((address_space(3))) s16x4_t*)(rows + tr_off[j]);
+        tr[2 * j] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(at);
+        tr[2 * j + 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(at);
       }
     };
-    {
-      bool cur_hit = false;
-      int64_t cur = next_tile(cur_hit);
-      int buf = 0;
-      if (cur >= 0) {
-        stage(cur);
-        store(0);
+    auto sum_tile = [&](int buf) {
+      // Dot products: lane holds p for queries 4kg..4kg+3 and entry ent of each
+      // chunk (A rows: dout of the tile's query ent).
+      f32x4_t d[SUB];
+#pragma unroll
+      for (int u = 0; u < SUB; ++u) {
+        d[u] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+          d[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, dr[s]), frag8(vfr[u][s]).v, d[u], 0, 0, 0);
       }
-      __syncthreads();
-      while (cur >= 0) {
-        bool nxt_hit = false;
-        const int64_t nxt = next_tile(nxt_hit);
-        if (nxt >= 0) stage(nxt);
-        if (cur_hit) {
-          touched = true;
-          sum_tile(cur, buf);
+      float aw[SUB][4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const uint4 h0 = *reinterpret_cast<const uint4*>(&s_rec[wave][buf][kg * 4 + r][0]);
+        const uint4 h1 = *reinterpret_cast<const uint4*>(&s_rec[wave][buf][kg * 4 + r][4]);
+        const float qx = __uint_as_float(h0.x << 16);
+        const float qy = __uint_as_float(h0.x & 0xFFFF0000u);
+        const float qz = __uint_as_float(h0.y << 16);
+        const float zinv = __uint_as_float(h0.z), cc = __uint_as_float(h0.w);
+#pragma unroll
+        for (int u = 0; u < SUB; ++u) {
+          const float df[3] = {qx - kv[u][0], qy - kv[u][1], qz - kv[u][2]};
+          const float d2 = fmaf(df[2], df[2], fmaf(df[1], df[1], fmaf(df[0], df[0], eps)));
+          const bool in = (uint32_t(e[u]) - h1.x <= h1.y) & (uint32_t(pos_e[u]) <= h1.z);
+          const float sc = in ? __builtin_amdgcn_rcpf(d2) : 0.0f;
+          aw[u][r] = sc * zinv;
+          const float w = (d[u][r] - cc) * sc * aw[u][r];
+#pragma unroll
+          for (int a = 0; a < 3; ++a) gk[u][a] = fmaf(w, df[a], gk[u][a]);
         }
-        if (nxt >= 0) store(buf ^ 1);
-        __syncthreads();
-        cur = nxt;
-        cur_hit = nxt_hit;
-        buf ^= 1;
+      }
+      // dv^T += dout^T (columns x queries) * A (queries x entries), high and
+      // low parts of A in one product per 16 columns (the K halves hold the
+      // same dout fragment).
+      Frag8 b[SUB];
+#pragma unroll
+      for (int u = 0; u < SUB; ++u) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const bf16x2_t h = {(__bf16)aw[u][2 * t], (__bf16)aw[u][2 * t + 1]};
+          uint32_t hw = __builtin_bit_cast(uint32_t, h);
+          asm("" : "+v"(hw));  // the packed pair, reused as is (one conversion)
+          const bf16x2_t l = {(__bf16)(aw[u][2 * t] - __uint_as_float(hw << 16)),
+                              (__bf16)(aw[u][2 * t + 1] - __uint_as_float(hw & 0xFFFF0000u))};
+          b[u].w[t] = hw;
+          b[u].w[t + 2] = __builtin_bit_cast(uint32_t, l);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < E; ++j) {
+        const bf16x8_t a8 = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(tr[2 * j], tr[2 * j + 1], 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+        for (int u = 0; u < SUB; ++u) acc[u][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, b[u].v, acc[u][j], 0, 0, 0);
+      }
+    };
+    const int32_t head = next_tile();
+    const bool touched = head >= 0;
+    if (touched) {
+      load_rec(head);
+      stage(head, 0);
+      int32_t nxt = next_tile();
+      if (nxt >= 0) load_rec(nxt);
+      // The tile in buffer `buf` is read whole first; then the next tile's
+      // copies into the other buffer are issued and the records of the one
+      // after it loaded (reads issued after the copies would wait for them),
+      // and the tile is summed meanwhile.
+      for (int buf = 0;; buf ^= 1) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this tile's rows (and the next one's records) have landed
+        read_tile(buf);
+        const bool more = nxt >= 0;
+        if (more) {
+          stage(nxt, buf ^ 1);
+          nxt = next_tile();
+          if (nxt >= 0) load_rec(nxt);
+        }
+        wave_lds_sync();
+        sum_tile(buf);
+        if (!more) break;
       }
     }
 
-    // Write (full list) or add (prefix lists) this chunk's rows: lane holds
-    // elements 4kg*E .. 4kg*E + 4E - 1 of entry ent's dv row.
+    // Write (full list) or add (prefix lists) these chunks' rows: lane holds
+    // columns 16j + 4kg .. + 3 of entry ent's dv row for every block j.
 #pragma unroll
-    for (int a = 0; a < 3; ++a) gk[a] = 2.0f * kg_sum(gk[a]);
-    if (valid_e && (first || touched)) {
-      float* drow = dv + (seg * N + pos_e) * int64_t(DV) + kg * 4 * E;
+    for (int u = 0; u < SUB; ++u) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if constexpr (E % 4 == 0) {
+      for (int a = 0; a < 3; ++a) gk[u][a] = 2.0f * kg_sum(gk[u][a]);
+      if (e[u] < L.n && (first || touched)) {
+        float* drow = dv + (seg * N + pos_e[u]) * int64_t(DV) + kg * 4;
+        if (!first) {
+          float4 old[E];
 #pragma unroll
-          for (int j0 = 0; j0 < E; j0 += 4) {
-            float4 o = make_float4(acc[j0][r], acc[j0 + 1][r], acc[j0 + 2][r], acc[j0 + 3][r]);
-            float4* dst = reinterpret_cast<float4*>(drow + r * E + j0);
-            if (!first) {
-              const float4 old = *dst;
-              o.x += old.x;
-              o.y += old.y;
-              o.z += old.z;
-              o.w += old.w;
-            }
-            *dst = o;
-          }
-        } else {
-          static_assert(E == 2, "d_v of 32 gives two elements per row and lane");
-          float2 o = make_float2(acc[0][r], acc[1][r]);
-          float2* dst = reinterpret_cast<float2*>(drow + r * E);
-          if (!first) {
-            const float2 old = *dst;
-            o.x += old.x;
-            o.y += old.y;
-          }
-          *dst = o;
+          for (int j = 0; j < E; ++j) old[j] = *reinterpret_cast<const float4*>(drow + 16 * j);
+#pragma unroll
+          for (int j = 0; j < E; ++j)
+            acc[u][j] += f32x4_t{old[j].x, old[j].y, old[j].z, old[j].w};
+        }
+#pragma unroll
+        for (int j = 0; j < E; ++j)
+          *reinterpret_cast<float4*>(drow + 16 * j) = make_float4(acc[u][j][0], acc[u][j][1], acc[u][j][2], acc[u][j][3]);
+        if (kg == 0) {
+          float* krow = dk + (seg * N + pos_e[u]) * 3;
+#pragma unroll
+          for (int a = 0; a < 3; ++a) krow[a] = first ? gk[u][a] : krow[a] + gk[u][a];
         }
       }
-      if (kg == 0) {
-        float* krow = dk + (seg * N + pos_e) * 3;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) krow[a] = first ? gk[a] : krow[a] + gk[a];
-      }
     }
-    // The next group reuses the LDS buffers.
-    __syncthreads();
+    // The next chunks' copies reuse the buffers once every read is done.
+    wave_lds_sync();
   }
 }
 
@@ -798,7 +862,6 @@ hipError_t launch_tile_bwd_t(const uint16_t* q, const uint16_t* v, const uint16_
   const int nl = tile_bwd_levels(N, topk, causal);
   const bool off32 = N * int64_t(DV) * 2 <= int64_t(0xFFFFFFFF);
   SlotRec* rec = reinterpret_cast<SlotRec*>(wsb + ws.rec_off);
-  uint16_t* dslot = reinterpret_cast<uint16_t*>(wsb + ws.dslot_off);
   float* part = reinterpret_cast<float*>(wsb + ws.part_off);
   int2* env = reinterpret_cast<int2*>(wsb + ws.env_off);
   int2* env2 = reinterpret_cast<int2*>(wsb + ws.env2_off);
@@ -817,14 +880,21 @@ hipError_t launch_tile_bwd_t(const uint16_t* q, const uint16_t* v, const uint16_
     const int64_t tiles = S * ct;
     const int64_t want = ceil_div(tiles, int64_t(kBtWaves));
     const unsigned blocks = unsigned(want < (int64_t(1) << 20) ? want : (int64_t(1) << 20));
-#define ZETA_BT_QUERY(HIST)                                                                                     \
-  hipLaunchKernelGGL((bwd_tile_query_kernel<DV, HIST>), dim3(blocks), dim3(kBtWaves * 64), 0, stream, q, v, dout, perm, \
-                     list_pos, q_order, bounds, keys_full, keys_list, S, N, ct, cz, chunk, lp.t0, lp.t_hi, lp.levels,   \
-                     lp.cap, eps, dq, rec, dslot, part, env, hm.k, hm.v, hk, hv)
-    if (hm.k != nullptr)
-      ZETA_BT_QUERY(true);
-    else
-      ZETA_BT_QUERY(false);
+#define ZETA_BT_QUERY(OFF, HIST)                                                                                  \
+  hipLaunchKernelGGL((bwd_tile_query_kernel<DV, OFF, HIST>), dim3(blocks), dim3(kBtWaves * 64), 0, stream, q, v, dout, \
+                     perm, list_pos, q_order, bounds, keys_full, keys_list, S, N, ct, cz, chunk, lp.t0, lp.t_hi,        \
+                     lp.levels, lp.cap, eps, dq, rec, part, env, hm.k, hm.v, hk, hv)
+    if (off32) {
+      if (hm.k != nullptr)
+        ZETA_BT_QUERY(true, true);
+      else
+        ZETA_BT_QUERY(true, false);
+    } else {
+      if (hm.k != nullptr)
+        ZETA_BT_QUERY(false, true);
+      else
+        ZETA_BT_QUERY(false, false);
+    }
 #undef ZETA_BT_QUERY
   }
   hipLaunchKernelGGL(bwd_envelope_kernel, dim3(unsigned(int64_t(nl) * S)), dim3(kEnvThreads), 0, stream, env, ct,
@@ -836,11 +906,11 @@ hipError_t launch_tile_bwd_t(const uint16_t* q, const uint16_t* v, const uint16_
   for (int li = nl - 1; li >= 0; --li) {
     const int lvl = !causal ? 0 : (li == lp.levels ? lp.t_hi + 1 : lp.t0 + li);
     const int64_t ln = (causal && lvl <= lp.t_hi) ? (int64_t(1) << lvl) : N;
-    const int64_t want = S * ceil_div(ceil_div(ln, int64_t(16)), int64_t(kKeyWaves));  // groups of chunks
+    const int64_t want = ceil_div(S * ceil_div(ceil_div(ln, int64_t(16)), int64_t(kKeySub<DV>)), int64_t(kKeyWaves));
     const unsigned blocks = unsigned(want < (int64_t(1) << 20) ? want : (int64_t(1) << 20));
 #define ZETA_BT_KEY(OFF)                                                                                       \
-  hipLaunchKernelGGL((bwd_tile_key_kernel<DV, OFF>), dim3(blocks), dim3(kKeyThreads), 0, stream, v, perm, list_pos,    \
-                     keys_full, keys_list, rec, dslot, env, ranges, S, N, ct, cz, lp.t0, lp.t_hi, lp.levels, lp.cap,  \
+  hipLaunchKernelGGL((bwd_tile_key_kernel<DV, OFF>), dim3(blocks), dim3(kKeyThreads), 0, stream, v, dout, perm,        \
+                     list_pos, keys_full, keys_list, rec, env, ranges, S, N, ct, cz, lp.t0, lp.t_hi, lp.levels, lp.cap,  \
                      lvl, li == nl - 1 ? 1 : 0, eps, dk, dv)
     if (off32)
       ZETA_BT_KEY(true);

@@ -56,7 +56,7 @@ namespace {
 
 constexpr int kBtWaves = 4;          // wavefronts per block
 constexpr int kBtChunk = kChunk;      // list entries per product step
-constexpr int kRedThreads = 256;
+constexpr int kRedThreads = 1024;
 constexpr uint32_t kNoList = 0xFFFFu;  // record of a slot whose query has no window
 
 // What the key pass needs of a slot's query, in 32 bytes: q as bfloat16 bits,
@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
                           const int32_t* __restrict__ list_pos, const int32_t* __restrict__ order,
                           const int2* __restrict__ bounds, const uint2* __restrict__ keys_full,
                           const uint2* __restrict__ keys_list, int64_t S, int64_t N, int64_t ct, int causal,
-                          int chunk, int t0, int t_hi, int levels, int64_t cap, float eps, float* __restrict__ dq,
+                          int chunk, int t0, int t_hi, int levels, int nl, int64_t cap, float eps, float* __restrict__ dq,
                           SlotRec* __restrict__ rec, float* __restrict__ deps_part,
                           int2* __restrict__ env, const float* __restrict__ mk, const float* __restrict__ mv,
                           float* __restrict__ hk, float* __restrict__ hv) {
@@ -212,14 +212,17 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
         my_b = bb.y;
       }
     }
-    // Slots without a query still hold a defined record and deps part.
+    // Slots without a query still hold a defined record.
     if (xs < N && my_i < 0 && kg == 0) {
       SlotRec r = {};
       r.q2_list = kNoList << 16;
       r.a = INT32_MIN;
       rec[slot] = r;
-      deps_part[slot] = 0.0f;
     }
+    // Lane l: the tile's window range in list l (empty so far), and this
+    // lane's query's part of deps.
+    int2 my_env = make_int2(INT32_MAX, INT32_MIN);
+    float my_deps = 0.0f;
     uint32_t pending = uint32_t(wave_ballot(my_i >= 0)) & 0xFFFFu;
 
     // Queries that search one list form a group (nearly always the whole tile).
@@ -237,7 +240,7 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
       {
         const int lo = wave_min_int(mine ? my_a : INT32_MAX);
         const int hi = wave_max_int(mine ? my_b : INT32_MIN);
-        if (lane == 0) env[(int64_t(level_index(g_lvl, causal, t0, t_hi, levels)) * S + seg) * ct + tau] = make_int2(lo, hi);
+        if (lane == level_index(g_lvl, causal, t0, t_hi, levels)) my_env = make_int2(lo, hi);
       }
 
       float qv[3] = {0.0f, 0.0f, 0.0f};
@@ -434,7 +437,7 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
         const int64_t gq = seg * N + my_i;
 #pragma unroll
         for (int a = 0; a < 3; ++a) dq[gq * 3 + a] = -2.0f * inv * (u[a] - cc * rr[a]);
-        deps_part[slot] = -inv * (xz - cc * yz);
+        my_deps = -inv * (xz - cc * yz);
         SlotRec r;
         r.q01 = (__float_as_uint(qv[0]) >> 16) | (__float_as_uint(qv[1]) & 0xFFFF0000u);
         const uint32_t list = mine ? uint32_t(level_index(g_lvl, causal, t0, t_hi, levels)) : kNoList;
@@ -448,6 +451,11 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
         rec[slot] = r;
       }
     }
+    if (lane < nl) env[(int64_t(lane) * S + seg) * ct + tau] = my_env;
+    // The tile's part of deps: lanes 0..15 hold the queries', summed as a tree.
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) my_deps += __shfl_xor(my_deps, off, 64);
+    if (lane == 0) deps_part[tile] = my_deps;
   }
 }
 
@@ -534,6 +542,98 @@ __global__ void __launch_bounds__(256)
   const int hi_c = int(c * 16 + 15 < ln - 1 ? c * 16 + 15 : ln - 1);
   const int2* ev2 = env2 + row * ct;
   ranges[t] = make_int2(int(first_at_least<true>(ev2, ct, lo_c)), int(first_at_least<false>(ev2, ct, hi_c + 1)));
+}
+
+// Envelopes and candidate ranges of a (list, segment) in one workgroup, for
+// segments of up to kEnvLdsTiles tiles: the envelopes stay in LDS (a thread
+// scans PER consecutive tiles in registers, wavefronts and the block are joined
+// by shuffles), where both binary searches of a chunk then run, instead of
+// through memory in two launches (16 x 65536: 17.5 + 12.5 -> 13.8 us).
+constexpr int64_t kEnvLdsTiles = 8192;
+
+template <int THREADS, int PER>
+__global__ void __launch_bounds__(THREADS)
+    bwd_envelope_ranges_kernel(const int2* __restrict__ env, int64_t S, int64_t N, int ct, int causal, int t0, int t_hi,
+                               int levels, int2* __restrict__ ranges) {
+  constexpr int kWaves = THREADS / 64;
+  __shared__ int s_mx[THREADS * PER];  // running maximum of the tiles' last indices
+  __shared__ int s_mn[THREADS * PER];  // running minimum, from the last tile, of their first indices
+  __shared__ int s_wmx[kWaves], s_wmn[kWaves];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int64_t row = blockIdx.x;  // list * S + segment
+  const int li = int(row / S);
+  const int lvl = !causal ? 0 : (li == levels ? t_hi + 1 : t0 + li);
+  const int ln = (causal && lvl <= t_hi) ? (1 << lvl) : int(N);
+  const int2* in = env + row * ct;
+  int2 r[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int t = tid * PER + j;
+    const int2 x = in[t < ct ? t : ct - 1];
+    r[j] = t < ct ? x : make_int2(INT32_MAX, INT32_MIN);
+  }
+  int mx = INT32_MIN, mn = INT32_MAX;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    mx = r[j].y > mx ? r[j].y : mx;
+    mn = r[j].x < mn ? r[j].x : mn;
+  }
+  // Inclusive scans over the threads: maximum upwards, minimum downwards.
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int a = __shfl_up(mx, off, 64), b = __shfl_down(mn, off, 64);
+    if (lane >= off) mx = a > mx ? a : mx;
+    if (lane + off < 64) mn = b < mn ? b : mn;
+  }
+  if (lane == 63) s_wmx[wave] = mx;
+  if (lane == 0) s_wmn[wave] = mn;
+  int before = __shfl_up(mx, 1, 64), after = __shfl_down(mn, 1, 64);
+  if (lane == 0) before = INT32_MIN;
+  if (lane == 63) after = INT32_MAX;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    if (w < wave) before = s_wmx[w] > before ? s_wmx[w] : before;
+    if (w > wave) after = s_wmn[w] < after ? s_wmn[w] : after;
+  }
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    before = r[j].y > before ? r[j].y : before;
+    s_mx[tid * PER + j] = before;
+  }
+#pragma unroll
+  for (int j = PER - 1; j >= 0; --j) {
+    after = r[j].x < after ? r[j].x : after;
+    s_mn[tid * PER + j] = after;
+  }
+  __syncthreads();
+  const int chunks = (ln + 15) / 16;
+  for (int c = tid; c < chunks; c += THREADS) {
+    const int lo_c = c * 16;
+    const int hi_c = c * 16 + 15 < ln - 1 ? c * 16 + 15 : ln - 1;
+    // First tiles with maximum >= lo_c and with minimum >= hi_c + 1, halving
+    // both at once (the tiles past ct hold the neutral ends).
+    int a0 = 0, a1 = ct, b0 = 0, b1 = ct;
+    while (a0 < a1 || b0 < b1) {
+      const int am = (a0 + a1) >> 1, bm = (b0 + b1) >> 1;
+      const int av = s_mx[am < ct ? am : ct - 1], bv = s_mn[bm < ct ? bm : ct - 1];
+      if (a0 < a1) {
+        if (av >= lo_c)
+          a1 = am;
+        else
+          a0 = am + 1;
+      }
+      if (b0 < b1) {
+        if (bv >= hi_c + 1)
+          b1 = bm;
+        else
+          b0 = bm + 1;
+      }
+    }
+    ranges[row * ct + c] = make_int2(a0, b0);
+  }
 }
 
 // ---- 3. key pass ------------------------------------------------------------------
@@ -829,14 +929,28 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
 }
 
 // ---- deps -----------------------------------------------------------------------
-// Fixed-order sum of the per-slot parts: block sums, then one block over them.
+// Fixed-order sum of the tiles' parts: one block when there are at most
+// kRedOne of them, else block sums first and then one block over those.
+constexpr int64_t kRedOne = int64_t(1) << 17;
+
 __global__ void __launch_bounds__(kRedThreads)
     bwd_tile_reduce_kernel(const float* __restrict__ part, int64_t n, int64_t per_block, float* __restrict__ sums) {
   __shared__ float s_red[kRedThreads];
   const int64_t b0 = int64_t(blockIdx.x) * per_block;
   const int64_t b1 = b0 + per_block < n ? b0 + per_block : n;
+  // Independent loads in batches, so their latencies overlap.
+  constexpr int kBatch = 16;
   float acc = 0.0f;
-  for (int64_t t = b0 + threadIdx.x; t < b1; t += kRedThreads) acc += part[t];
+  for (int64_t t = b0 + threadIdx.x; t < b1; t += kBatch * kRedThreads) {
+    float x[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int64_t e = t + j * kRedThreads;
+      x[j] = part[e < b1 ? e : t];
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) acc += t + j * kRedThreads < b1 ? x[j] : 0.0f;
+  }
   s_red[threadIdx.x] = acc;
   __syncthreads();
   for (int w = kRedThreads / 2; w > 0; w >>= 1) {
@@ -844,11 +958,6 @@ __global__ void __launch_bounds__(kRedThreads)
     __syncthreads();
   }
   if (threadIdx.x == 0) sums[blockIdx.x] = s_red[0];
-}
-
-__global__ void __launch_bounds__(256) bwd_tile_fill_int2_kernel(int2* __restrict__ p, int64_t n, int2 val) {
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < n; t += stride) p[t] = val;
 }
 
 template <int DV>
@@ -870,11 +979,6 @@ hipError_t launch_tile_bwd_t(const uint16_t* q, const uint16_t* v, const uint16_
   float* hv = reinterpret_cast<float*>(wsb + ws.hist_v_off);
   float* sums = reinterpret_cast<float*>(wsb + ws.sums_off);
   const int64_t nenv = int64_t(nl) * S * ct;
-  {
-    const int64_t want = ceil_div(nenv, int64_t(256));
-    hipLaunchKernelGGL(bwd_tile_fill_int2_kernel, dim3(unsigned(want < 65536 ? want : 65536)), dim3(256), 0, stream,
-                       env, nenv, make_int2(INT32_MAX, INT32_MIN));
-  }
   const int cz = causal ? 1 : 0;
   {
     const int64_t tiles = S * ct;
@@ -883,7 +987,7 @@ hipError_t launch_tile_bwd_t(const uint16_t* q, const uint16_t* v, const uint16_
 #define ZETA_BT_QUERY(OFF, HIST)                                                                                  \
   hipLaunchKernelGGL((bwd_tile_query_kernel<DV, OFF, HIST>), dim3(blocks), dim3(kBtWaves * 64), 0, stream, q, v, dout, \
                      perm, list_pos, q_order, bounds, keys_full, keys_list, S, N, ct, cz, chunk, lp.t0, lp.t_hi,        \
-                     lp.levels, lp.cap, eps, dq, rec, part, env, hm.k, hm.v, hk, hv)
+                     lp.levels, nl, lp.cap, eps, dq, rec, part, env, hm.k, hm.v, hk, hv)
     if (off32) {
       if (hm.k != nullptr)
         ZETA_BT_QUERY(true, true);
@@ -897,10 +1001,26 @@ hipError_t launch_tile_bwd_t(const uint16_t* q, const uint16_t* v, const uint16_
     }
 #undef ZETA_BT_QUERY
   }
-  hipLaunchKernelGGL(bwd_envelope_kernel, dim3(unsigned(int64_t(nl) * S)), dim3(kEnvThreads), 0, stream, env, ct,
-                     env2);
-  hipLaunchKernelGGL(bwd_ranges_kernel, dim3(unsigned(ceil_div(nenv, int64_t(256)))), dim3(256), 0, stream, env2, S, N,
-                     ct, cz, lp.t0, lp.t_hi, lp.levels, nl, ranges);
+  if (ct <= kEnvLdsTiles) {
+    const dim3 grid(unsigned(int64_t(nl) * S));
+#define ZETA_BT_ENV(THREADS, PER)                                                                                \
+  hipLaunchKernelGGL((bwd_envelope_ranges_kernel<THREADS, PER>), grid, dim3(THREADS), 0, stream, env, S, N, int(ct), \
+                     cz, lp.t0, lp.t_hi, lp.levels, ranges)
+    if (ct <= 256)
+      ZETA_BT_ENV(256, 1);
+    else if (ct <= 1024)
+      ZETA_BT_ENV(256, 4);
+    else if (ct <= 4096)
+      ZETA_BT_ENV(1024, 4);
+    else
+      ZETA_BT_ENV(1024, 8);
+#undef ZETA_BT_ENV
+  } else {
+    hipLaunchKernelGGL(bwd_envelope_kernel, dim3(unsigned(int64_t(nl) * S)), dim3(kEnvThreads), 0, stream, env, ct,
+                       env2);
+    hipLaunchKernelGGL(bwd_ranges_kernel, dim3(unsigned(ceil_div(nenv, int64_t(256)))), dim3(256), 0, stream, env2, S,
+                       N, ct, cz, lp.t0, lp.t_hi, lp.levels, nl, ranges);
+  }
   // The full list first (its launch writes every key's rows), then the prefix
   // lists from the longest down.
   for (int li = nl - 1; li >= 0; --li) {
@@ -923,7 +1043,11 @@ hipError_t launch_tile_bwd_t(const uint16_t* q, const uint16_t* v, const uint16_
     const hipError_t e = launch_history_spread(hv, dv, DV, hk, dk, 3, S, N, causal, wsb + ws.hist_scan_off, stream);
     if (e != hipSuccess) return e;
   }
-  const int64_t total = S * N;
+  const int64_t total = S * ct;
+  if (total <= kRedOne) {
+    hipLaunchKernelGGL(bwd_tile_reduce_kernel, dim3(1), dim3(kRedThreads), 0, stream, part, total, total, deps);
+    return hipGetLastError();
+  }
   const int64_t nred = ceil_div(total, kTileBwdRedPer) < kTileBwdRedMax ? ceil_div(total, kTileBwdRedPer)
                                                                         : kTileBwdRedMax;
   const int64_t per = ceil_div(total, nred);

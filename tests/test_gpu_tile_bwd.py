@@ -111,6 +111,21 @@ def test_tile_bwd_edges(shape, causal):
     _check(idx, got, f, oracle.as_f32(dout_raw, w.dtype), 0.3)
 
 
+@pytest.mark.parametrize("N", [4096, 4097, 16385, 65537, 131073])
+def test_tile_bwd_tile_counts(N):
+    """Segments around the tile counts (N / 16) at which the candidate ranges
+    of the key pass change kernels, the last in memory, with deps summed from
+    ragged last tiles."""
+    w = workloads.custom(B=1, H=1, N=N, dv=32, topk=8, dtype="bf16", bits=8, seed=N)
+    log(f"tile bwd tile counts N={N}")
+    x = workloads.generate(w)
+    raw = {n: a.reshape(1, N, -1) for n, a in x.items()}
+    f = {n: oracle.as_f32(a, w.dtype) for n, a in raw.items()}
+    dout_raw = workloads.generate_dout(w).reshape(1, N, w.dv)
+    idx, *got = _gpu(raw, dout_raw, w, True, 0.5)
+    _check(idx, got, f, oracle.as_f32(dout_raw, w.dtype), 0.5)
+
+
 def test_tile_bwd_orders_and_repeat():
     """Any processing order gives the oracle's gradients; dq and deps's parts
     depend only on each query's own window, so dq is bit-identical across

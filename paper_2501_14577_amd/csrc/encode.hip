@@ -9,11 +9,14 @@
 //     quantises and interleaves 256 query rows and 256 key rows, each row read
 //     with one load.  Quantisation is float32 with one rounding per operation,
 //     matching the definition bit for bit.
-// For d_k = 3 with 16-byte aligned tensors and N a multiple of 8 (every
-// workload here) both kernels take a vector form instead: a thread owns 8
-// consecutive rows, read as whole 16-byte vectors (24 values: three loads of
-// bfloat16, six of float32) and written as two 16-byte code stores; a block
-// covers 1024 rows of one segment (grid: chunks x segments, no index
+// For d_k = 3 and N >= 8 (every workload here) a vector form runs instead: a
+// thread owns 8 consecutive rows, read as whole 16-byte vectors (24 values:
+// three loads of bfloat16, six of float32) and written as two 16-byte code
+// stores, none of which needs more than the element's alignment; a segment's
+// last thread takes its last 8 rows, some of them a second time.  Segments of
+// up to 4096 rows take one launch: a workgroup holds a segment's rows in
+// registers, reduces their range and encodes them.  Longer ones take two, a
+// block covering 1024 rows of one segment (grid: chunks x segments, no index
 // division; up to 65535 segments).  The quotient of the quantiser comes from the hardware
 // reciprocal unless it lies close enough to an integer that the correctly
 // rounded division could floor differently; then the IEEE division decides
@@ -175,13 +178,23 @@ constexpr int kEnc3Threads = 128;
 constexpr int kEnc3Rows = 8;                                  // rows per thread
 constexpr int64_t kEnc3Chunk = int64_t(kEnc3Threads) * kEnc3Rows;  // rows per block
 
-// Rows r .. r+7 of a [rows][3] array whose row r starts on a 16-byte
-// boundary: 24 values.
+// 16 bytes at any address of T's alignment (one load or store: the hardware
+// takes global accesses of every alignment).
+template <typename T>
+__device__ __forceinline__ uint4 load16(const T* p) {
+  uint4 x;
+  __builtin_memcpy(&x, p, 16);
+  return x;
+}
+
+__device__ __forceinline__ void store16(uint32_t* p, uint4 x) { __builtin_memcpy(p, &x, 16); }
+
+// Rows r .. r+7 of a [rows][3] array: 24 values.
 template <typename T>
 __device__ __forceinline__ void load_rows8(const T* base, int64_t r, float (&x)[24]) {
-  const uint4* p = reinterpret_cast<const uint4*>(base + r * 3);
+  const T* p = base + r * 3;
   if constexpr (sizeof(T) == 2) {
-    const uint4 a = p[0], b = p[1], c = p[2];
+    const uint4 a = load16(p), b = load16(p + 8), c = load16(p + 16);
     const uint32_t w[12] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, c.x, c.y, c.z, c.w};
 #pragma unroll
     for (int i = 0; i < 12; ++i) {
@@ -191,7 +204,7 @@ __device__ __forceinline__ void load_rows8(const T* base, int64_t r, float (&x)[
   } else {
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
-      const uint4 v = p[i];
+      const uint4 v = load16(p + 4 * i);
       x[4 * i] = __uint_as_float(v.x);
       x[4 * i + 1] = __uint_as_float(v.y);
       x[4 * i + 2] = __uint_as_float(v.z);
@@ -200,10 +213,11 @@ __device__ __forceinline__ void load_rows8(const T* base, int64_t r, float (&x)[
   }
 }
 
-// Per-axis min and max of (lo[a], hi[a]) over the block (128 threads), result
-// in s_lo / s_hi.
-__device__ __forceinline__ void block128_range3(float (&lo)[3], float (&hi)[3], float* s_lo, float* s_hi) {
-  __shared__ float s_part[2][6];
+// Per-axis min and max of (lo[a], hi[a]) over the block (64 * kWaves threads),
+// result in s_lo / s_hi.
+template <int kWaves>
+__device__ __forceinline__ void block_range3(float (&lo)[3], float (&hi)[3], float* s_lo, float* s_hi) {
+  __shared__ float s_part[kWaves][6];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
 #pragma unroll
@@ -222,8 +236,14 @@ __device__ __forceinline__ void block128_range3(float (&lo)[3], float (&hi)[3], 
   }
   __syncthreads();
   if (threadIdx.x < 3) {
-    s_lo[threadIdx.x] = fminf(s_part[0][threadIdx.x], s_part[1][threadIdx.x]);
-    s_hi[threadIdx.x] = fmaxf(s_part[0][3 + threadIdx.x], s_part[1][3 + threadIdx.x]);
+    float l = s_part[0][threadIdx.x], h = s_part[0][3 + threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) {
+      l = fminf(l, s_part[w][threadIdx.x]);
+      h = fmaxf(h, s_part[w][3 + threadIdx.x]);
+    }
+    s_lo[threadIdx.x] = l;
+    s_hi[threadIdx.x] = h;
   }
   __syncthreads();
 }
@@ -240,10 +260,11 @@ __global__ void __launch_bounds__(kEnc3Threads)
     lo[a] = __builtin_huge_valf();
     hi[a] = -__builtin_huge_valf();
   }
-  if (r < N) {  // N is a multiple of 8: all 8 rows exist
+  if (r < N) {
+    const int64_t rr = r + kEnc3Rows <= N ? r : N - kEnc3Rows;
     float x[24], y[24];
-    load_rows8(q, seg * N + r, x);
-    load_rows8(k, seg * N + r, y);
+    load_rows8(q, seg * N + rr, x);
+    load_rows8(k, seg * N + rr, y);
 #pragma unroll
     for (int i = 0; i < 24; ++i) {
       lo[i % 3] = fminf(lo[i % 3], fminf(x[i], y[i]));
@@ -251,7 +272,7 @@ __global__ void __launch_bounds__(kEnc3Threads)
     }
   }
   __shared__ float s_lo[3], s_hi[3];
-  block128_range3(lo, hi, s_lo, s_hi);
+  block_range3<kEnc3Threads / 64>(lo, hi, s_lo, s_hi);
   if (threadIdx.x < 3) {
     float* out = partial + (seg * int64_t(gridDim.x) + chunk) * 6;
     out[threadIdx.x] = s_lo[threadIdx.x];
@@ -280,6 +301,75 @@ __device__ __forceinline__ uint32_t quantise_fast(float x, float lo, float den, 
   return uint32_t(f);
 }
 
+// Quantise and interleave 8 rows of q and of k, and write their codes (rows
+// `row` on of the code arrays).
+__device__ __forceinline__ void encode_rows8(const float (&xq)[24], const float (&xk)[24], const float* s_lo,
+                                             const float* s_hi, int bits, int64_t row, uint32_t* __restrict__ q_codes,
+                                             uint32_t* __restrict__ k_codes) {
+  const uint32_t top = (1u << bits) - 1u;
+  const float topf = float(top);
+  float lo[3], den[3], rden[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    lo[a] = s_lo[a];
+    {
+#pragma clang fp contract(off)
+      den[a] = s_hi[a] - s_lo[a];
+    }
+    rden[a] = __builtin_amdgcn_rcpf(den[a]);
+  }
+#pragma unroll
+  for (int which = 0; which < 2; ++which) {
+    const float(&x)[24] = which == 0 ? xq : xk;
+    uint32_t c[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t c0 = quantise_fast(x[3 * i], lo[0], den[0], rden[0], topf, top);
+      const uint32_t c1 = quantise_fast(x[3 * i + 1], lo[1], den[1], rden[1], topf, top);
+      const uint32_t c2 = quantise_fast(x[3 * i + 2], lo[2], den[2], rden[2], topf, top);
+      c[i] = (spread3(c0) << 2) | (spread3(c1) << 1) | spread3(c2);
+    }
+    uint32_t* dst = (which == 0 ? q_codes : k_codes) + row;
+    store16(dst, make_uint4(c[0], c[1], c[2], c[3]));
+    store16(dst + 4, make_uint4(c[4], c[5], c[6], c[7]));
+  }
+}
+
+// A segment of at most 8 * THREADS rows per workgroup: range and codes in one
+// launch, each row read once.  Bound: latency (one load, one block reduction)
+// and, for the longest, the workgroup's own vector issue.
+template <typename T, int THREADS>
+__global__ void __launch_bounds__(THREADS)
+    encode3_segment_kernel(const T* __restrict__ q, const T* __restrict__ k, int64_t N, int bits,
+                           float* __restrict__ range_out, uint32_t* __restrict__ q_codes,
+                           uint32_t* __restrict__ k_codes) {
+  const int64_t seg = blockIdx.x;
+  const int64_t r = int64_t(threadIdx.x) * kEnc3Rows;
+  // A thread past the segment's end reads its last rows and writes nothing.
+  const int64_t rr = r + kEnc3Rows <= N ? r : N - kEnc3Rows;
+  float xq[24], xk[24];
+  load_rows8(q, seg * N + rr, xq);
+  load_rows8(k, seg * N + rr, xk);
+  float lo[3], hi[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    lo[a] = fminf(xq[a], xk[a]);
+    hi[a] = fmaxf(xq[a], xk[a]);
+  }
+#pragma unroll
+  for (int i = 3; i < 24; ++i) {
+    lo[i % 3] = fminf(lo[i % 3], fminf(xq[i], xk[i]));
+    hi[i % 3] = fmaxf(hi[i % 3], fmaxf(xq[i], xk[i]));
+  }
+  __shared__ float s_lo[3], s_hi[3];
+  block_range3<THREADS / 64>(lo, hi, s_lo, s_hi);
+  if (range_out != nullptr && threadIdx.x < 3) {
+    range_out[seg * 6 + threadIdx.x] = s_lo[threadIdx.x];
+    range_out[seg * 6 + 3 + threadIdx.x] = s_hi[threadIdx.x];
+  }
+  if (r < N) encode_rows8(xq, xk, s_lo, s_hi, bits, seg * N + rr, q_codes, k_codes);
+}
+
 template <typename T>
 __global__ void __launch_bounds__(kEnc3Threads)
     encode3_kernel(const T* __restrict__ q, const T* __restrict__ k, int64_t N, int bits,
@@ -288,10 +378,10 @@ __global__ void __launch_bounds__(kEnc3Threads)
   const int64_t chunk = blockIdx.x, seg = blockIdx.y;
   const int64_t chunks = gridDim.x;
   // This thread's rows are loaded first, so that their latency overlaps the
-  // range fold (a thread past the segment's end reads its first rows, and
+  // range fold (a thread past the segment's end reads its last rows, and
   // writes nothing).
   const int64_t r = chunk * kEnc3Chunk + int64_t(threadIdx.x) * kEnc3Rows;
-  const int64_t rr = r < N ? r : 0;
+  const int64_t rr = r + kEnc3Rows <= N ? r : N - kEnc3Rows;
   float xq[24], xk[24];
   load_rows8(q, seg * N + rr, xq);
   load_rows8(k, seg * N + rr, xk);
@@ -318,51 +408,38 @@ __global__ void __launch_bounds__(kEnc3Threads)
         hi[a] = fmaxf(hi[a], p[c * 6 + 3 + a]);
       }
     }
-    block128_range3(lo, hi, s_lo, s_hi);
+    block_range3<kEnc3Threads / 64>(lo, hi, s_lo, s_hi);
   }
   if (range_out != nullptr && chunk == 0 && threadIdx.x < 3) {
     range_out[seg * 6 + threadIdx.x] = s_lo[threadIdx.x];
     range_out[seg * 6 + 3 + threadIdx.x] = s_hi[threadIdx.x];
   }
-  if (r >= N) return;
-  const uint32_t top = (1u << bits) - 1u;
-  const float topf = float(top);
-  float lo[3], den[3], rden[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    lo[a] = s_lo[a];
-    {
-#pragma clang fp contract(off)
-      den[a] = s_hi[a] - s_lo[a];
-    }
-    rden[a] = __builtin_amdgcn_rcpf(den[a]);
-  }
-#pragma unroll
-  for (int which = 0; which < 2; ++which) {
-    const float(&x)[24] = which == 0 ? xq : xk;
-    uint32_t c[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint32_t c0 = quantise_fast(x[3 * i], lo[0], den[0], rden[0], topf, top);
-      const uint32_t c1 = quantise_fast(x[3 * i + 1], lo[1], den[1], rden[1], topf, top);
-      const uint32_t c2 = quantise_fast(x[3 * i + 2], lo[2], den[2], rden[2], topf, top);
-      c[i] = (spread3(c0) << 2) | (spread3(c1) << 1) | spread3(c2);
-    }
-    uint4* dst = reinterpret_cast<uint4*>((which == 0 ? q_codes : k_codes) + seg * N + r);
-    dst[0] = make_uint4(c[0], c[1], c[2], c[3]);
-    dst[1] = make_uint4(c[4], c[5], c[6], c[7]);
-  }
+  if (r < N) encode_rows8(xq, xk, s_lo, s_hi, bits, seg * N + rr, q_codes, k_codes);
 }
-
-bool aligned16_ptr(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 template <typename T>
 hipError_t launch_encode_t(const T* q, const T* k, int64_t S, int64_t N, int dk, int bits,
                            const float* range_lohi, float* range_out, uint32_t* q_codes,
                            uint32_t* k_codes, void* workspace, hipStream_t stream) {
   const EncodeWs ws = encode_ws(S, N, dk);
-  if (dk == 3 && N % kEnc3Rows == 0 && S <= 65535 && aligned16_ptr(q) && aligned16_ptr(k) && aligned16_ptr(q_codes) &&
-      aligned16_ptr(k_codes)) {
+  // One launch up to 4096 rows: 128 segments of 4096 take 11.2 us against 14.9 in
+  // two.  At 8192 rows a workgroup's own arithmetic outlasts the launch saved (96
+  // segments: 16.5 against 15.6 us).
+  if (dk == 3 && N >= kEnc3Rows && N <= 4096 && range_lohi == nullptr) {
+    const dim3 grid{unsigned(S)};
+#define ZETA_ENC_SEGMENT(THREADS)                                                                                 \
+  hipLaunchKernelGGL((encode3_segment_kernel<T, THREADS>), grid, dim3(THREADS), 0, stream, q, k, N, bits, range_out, \
+                     q_codes, k_codes)
+    if (N <= 1024)
+      ZETA_ENC_SEGMENT(128);
+    else if (N <= 2048)
+      ZETA_ENC_SEGMENT(256);
+    else
+      ZETA_ENC_SEGMENT(512);
+#undef ZETA_ENC_SEGMENT
+    return hipGetLastError();
+  }
+  if (dk == 3 && N >= kEnc3Rows && S <= 65535) {
     // Vector form; its partials (one per 1024-row chunk) fit in the space
     // sized for 512-row chunks.
     const dim3 grid(unsigned(ceil_div(N, kEnc3Chunk)), unsigned(S));

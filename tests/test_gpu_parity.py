@@ -63,8 +63,8 @@ def _edge_values(lo, hi, bits):
 @pytest.mark.parametrize("pad8", [False, True])
 @pytest.mark.parametrize("bits,lo,hi", [(10, -1.7, 2.3), (6, -3.1, 0.9), (10, 0.1, 0.30000001), (2, -1.0, 1.0)])
 def test_encode_bucket_edges(bits, lo, hi, pad8):
-    """pad8: a length that is a multiple of 8 (the vector form of the d_k = 3
-    kernels), else a ragged one (the row-per-thread form)."""
+    """pad8: a length that is a multiple of 8 (whole 8-row threads of the d_k =
+    3 kernels), else a ragged one (the last thread repeats rows)."""
     log(f"encode edges bits={bits} lo={lo} hi={hi} pad8={pad8}")
     vals = _edge_values(lo, hi, bits)
     vals = np.concatenate([vals, np.float32([lo - 1, hi + 1])])  # outside the range: clamps
@@ -99,6 +99,34 @@ def test_encode_shapes(dk, bits, dtype, N):
     torch.cuda.synchronize()
     assert np.array_equal(host(qc).reshape(S, w.N), eq)
     assert np.array_equal(host(kc).reshape(S, w.N), ek)
+
+
+@pytest.mark.parametrize("N", [7, 8, 9, 1023, 1025, 2049, 4097, 8191, 8192, 8193, 9001])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_encode_workgroup_edges(N, dtype):
+    """Segment lengths around each workgroup size of the one-launch encode and
+    of the two-launch one, ragged ends, and tensors that start one element off
+    their allocation (rows at no more than the element's alignment)."""
+    log(f"encode workgroup edges N={N} {dtype}")
+    w = workloads.custom(B=1, H=3, N=N, dk=3, dtype=dtype, bits=10, seed=N)
+    x = workloads.generate(w, with_v=False)
+    qf, kf = (oracle.as_f32(x[n], dtype).reshape(3, N, 3) for n in ("q", "k"))
+    eq, ek, lo, hi = oracle.morton_encode(qf, kf, 10)
+
+    def off_by_one(t):
+        flat = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        flat[1:] = t.reshape(-1)
+        return flat[1:].view(t.shape)
+
+    q, k = (to_dev(x[n], dtype) for n in ("q", "k"))
+    for a, b in ((q, k), (off_by_one(q), off_by_one(k))):
+        rng_out = torch.empty((3, 2, 3), dtype=torch.float32, device=q.device)
+        qc, kc = zeta.zeta_morton_encode(a, b, 10, range_out=rng_out)
+        given = zeta.zeta_morton_encode(a, b, 10, range_lohi=rng_out)
+        torch.cuda.synchronize()
+        assert np.array_equal(host(qc).reshape(3, N), eq) and np.array_equal(host(kc).reshape(3, N), ek)
+        assert np.array_equal(host(given[0]).reshape(3, N), eq) and np.array_equal(host(given[1]).reshape(3, N), ek)
+        assert np.array_equal(host(rng_out), np.stack([lo, hi], axis=1))
 
 
 def test_encode_constant_inputs():

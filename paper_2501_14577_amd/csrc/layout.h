@@ -50,6 +50,9 @@ inline bool block_sort_path(int64_t S, int64_t N) { return N <= 8192 || (N <= 16
 
 // ---- select ---------------------------------------------------------------
 constexpr int kMaxLevels = 32;
+// Up to this many keys per segment a prefix-list tile counts the earlier tiles'
+// entries itself.
+constexpr int64_t kListInline = 4096;
 
 // ---- attend ---------------------------------------------------------------
 constexpr int kAttWavesPerBlock = 8;

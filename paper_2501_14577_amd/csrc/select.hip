@@ -14,7 +14,9 @@
 // the result is the definition's, not an approximation of it.
 //
 // Kernels:
-//   list_count:   per tile of the sorted list, how many keys fall in each F_t;
+//   list_count:   per tile of the sorted list, how many keys fall in each F_t
+//                 (segments of up to kListInline keys leave it out: their few
+//                 tiles count the earlier entries themselves);
 //   list_scatter: stable compaction of each tile into every F_t it feeds
 //                 (one ballot per level and 64 keys; earlier tiles' counts
 //                 give the base);
@@ -83,7 +85,35 @@ __global__ void __launch_bounds__(kSortThreads)
   __shared__ uint32_t s_before[kGroups][kMaxLevels];           // entries of earlier tiles, by tile group
   __shared__ uint32_t s_wave[kSortThreads / 64][kMaxLevels];  // per-wave counts, then prefixes
 
-  {
+  if (cnt == nullptr) {
+    // Entries of the earlier tiles per level, counted here: each wavefront
+    // takes every 4th chunk of 64 entries, lane l keeps level l's count.
+    constexpr int kWaves = kSortThreads / 64, kBatch = 8;
+    const int chunks = int(tile) * int(kSortTile / 64);
+    const int32_t* ps = perm + seg * N;
+    uint32_t b = 0;
+    for (int c0 = wave; c0 < chunks; c0 += kBatch * kWaves) {
+      int32_t p[kBatch];
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        const int c = c0 + j * kWaves;
+        const int32_t x = ps[(c < chunks ? c : 0) * 64 + lane];
+        p[j] = c < chunks ? x : 0x7FFFFFFF;
+      }
+      for (int l = 0; l < levels; ++l) {
+        const int32_t lim = int32_t(1) << (t0 + l);
+        uint32_t n = 0;
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) n += uint32_t(__popcll(wave_ballot(p[j] < lim)));
+        b += lane == l ? n : 0u;
+      }
+    }
+    static_assert(kGroups == 2 * kWaves && kMaxLevels <= 64, "a row of counts per wavefront, the other rows empty");
+    if (lane < kMaxLevels) {
+      s_before[wave][lane] = b;
+      s_before[kWaves + wave][lane] = 0u;
+    }
+  } else {
     // Entries of the earlier tiles per level: thread (g, l) sums the tiles
     // t < tile with t % kGroups == g.
     const int l = tid % kMaxLevels, g = tid / kMaxLevels;
@@ -226,7 +256,13 @@ hipError_t launch_prefix_lists(const uint32_t* sorted_codes, const int32_t* perm
   int32_t* lpos = reinterpret_cast<int32_t*>(wsb + ws.pos_off);
   const int64_t tiles = ceil_div(N, kSortTile);
   const dim3 grid(unsigned(S * tiles)), block(kSortThreads);
-  hipLaunchKernelGGL(list_count_kernel, grid, block, 0, stream, perm, N, tiles, lp.t0, lp.levels, cnt);
+  // Counting the earlier entries again costs a tile up to 48 chunks of 64 at
+  // 4096 keys, the launch it saves 4-5 us; at 8192 keys the two are even or worse
+  // (a forward of 96 x 8192: 205.7 against 203.7 us).
+  if (N <= kListInline)
+    cnt = nullptr;
+  else
+    hipLaunchKernelGGL(list_count_kernel, grid, block, 0, stream, perm, N, tiles, lp.t0, lp.levels, cnt);
   hipLaunchKernelGGL(list_scatter_kernel, grid, block, 0, stream, sorted_codes, perm, N, tiles, lp.t0, lp.levels,
                      lp.cap, cnt, lc, lpos, k_rows, keys_full, keys_list);
   *list_codes = lc;

@@ -505,7 +505,7 @@ def test_forward_zorder_matches_position_order():
 
 @pytest.mark.parametrize("N,topk,causal,chunk", [(65, 1, True, 0), (1000, 1, True, 0), (1000, 40, True, 0),
                                                  (1000, 40, True, 93), (777, 16, False, 0), (3001, 1024, True, 0),
-                                                 (700, 128, True, 0)])
+                                                 (700, 128, True, 0), (4096, 16, True, 0), (4097, 16, True, 0)])
 def test_select_runs_over_several_lists(N, topk, causal, chunk):
     """Runs of 64 slots that cross segments and list levels (N not a multiple
     of 64; k = 1: a list per power of two), in the level-regrouped Z-order (a

@@ -12,6 +12,10 @@ constexpr int kMaxDk = 8;       // largest d_k compiled
 constexpr int kMaxTopk = 1024;  // largest k compiled
 constexpr int kMaxBits = 24;    // grid cells per axis stay exact in float32
 
+inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
+
+inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
 // ---- encode ---------------------------------------------------------------
 // Rows of q (and of k) reduced by one block of the range kernel.
 constexpr int64_t kEncRowsPerChunk = 512;
@@ -47,6 +51,20 @@ constexpr int64_t kRadixInlineTiles = 32;
 // 32768 keys a workgroup's registers spill and it loses at any number (46 ->
 // 100 us for 16 segments).
 inline bool block_sort_path(int64_t S, int64_t N) { return N <= 8192 || (N <= 16384 && S >= 100); }
+// Whether longer segments are sorted as runs of kMergeRun keys, one workgroup
+// each, and merged.  The runs cost 17 us (30-bit codes, four passes; 10 us in
+// two passes) and the merge about 5 us and 6.5 us per million searches (elements
+// times the other runs); tiled passes cost 11 us each while they are bound by
+// their launches.  Measured, passes -> merge: 30 bits, 32 x 10007 44.3 -> 28.2, 16 x
+// 20011 44.5 -> 32.8, 32 x 20011 46.7 -> 44.0, 16 x 32768 45.2 -> 45.8; 18 bits, 16
+// x 16384 23.7 -> 21.9, 16 x 20011 23.8 -> 25.7 us.
+constexpr int64_t kMergeRun = 4096;
+constexpr int kMergeRuns = 8;
+inline bool merge_sort_path(int64_t S, int64_t N, int passes) {
+  if (passes < 2 || N <= 8192 || N > kMergeRun * kMergeRuns) return false;
+  const int64_t searches = N * (ceil_div(N, kMergeRun) - 1);  // per segment
+  return S <= (passes > 2 ? 5 << 19 : 3 << 18) / searches;
+}
 
 // ---- select ---------------------------------------------------------------
 constexpr int kMaxLevels = 32;
@@ -56,10 +74,6 @@ constexpr int64_t kListInline = 4096;
 
 // ---- attend ---------------------------------------------------------------
 constexpr int kAttWavesPerBlock = 8;
-
-inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
-
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Smallest t with 2^t >= x (x >= 1).
 inline int ceil_log2(int64_t x) {

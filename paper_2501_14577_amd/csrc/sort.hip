@@ -20,7 +20,8 @@
 // several tiles write into the same output lines merge in that XCD's L2.
 // Segments of up to 8192 keys (16384 when there are many; block_sort_path)
 // take one launch instead: a workgroup holds a whole segment in registers and
-// runs every pass on it (block_sort).
+// runs every pass on it (block_sort).  Somewhat longer ones, when few, are
+// sorted so in runs of 4096 keys and merged (merge_sort_path).
 // A pass preserves the order of equal digits, so after the last pass equal
 // codes are in ascending position order.  ceil(code_bits / 9) passes split
 // the bits evenly (18-bit codes: two passes of 9).
@@ -292,8 +293,8 @@ __global__ void __launch_bounds__(kRadixThreads)
 // level partition, 8192 x 256, 18.8 -> 10.7.
 template <int THREADS, int KPT, bool kByLevel>
 __global__ void __launch_bounds__(THREADS)
-    block_sort_kernel(const uint32_t* __restrict__ keys, const int32_t* __restrict__ vals, int64_t N, int code_bits,
-                      int digit_bits, int t0, int t_hi, int chunk, uint32_t* __restrict__ keys_out,
+    block_sort_kernel(const uint32_t* __restrict__ keys, const int32_t* __restrict__ vals, int64_t N, int runs,
+                      int code_bits, int digit_bits, int t0, int t_hi, int chunk, uint32_t* __restrict__ keys_out,
                       int32_t* __restrict__ pos_out) {
   constexpr int kWaves = THREADS / 64;
   constexpr int kCap = THREADS * KPT;
@@ -305,8 +306,11 @@ __global__ void __launch_bounds__(THREADS)
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int64_t off = int64_t(blockIdx.x) * N;
-  const int n = int(N);
+  // This workgroup's keys: the segment, or one of its `runs` stretches of kCap.
+  const int64_t seg = blockIdx.x / unsigned(runs);
+  const int base = int(blockIdx.x % unsigned(runs)) * kCap;
+  const int64_t off = seg * N + base;
+  const int n = runs == 1 ? int(N) : int(N - base < kCap ? N - base : kCap);
   const int first = wave * (KPT * 64) + lane;  // element c of this thread: first + 64 c
 
   uint32_t key[KPT];
@@ -316,7 +320,7 @@ __global__ void __launch_bounds__(THREADS)
     const int e = first + c * 64;
     const int ec = e < n ? e : n - 1;
     if (kByLevel)
-      key[c] = vals != nullptr ? uint32_t(vals[off + ec]) : uint32_t(ec);
+      key[c] = vals != nullptr ? uint32_t(vals[off + ec]) : uint32_t(ec);  // one run
     else
       key[c] = keys[off + ec];
     pos[c] = uint32_t(e);
@@ -402,7 +406,7 @@ __global__ void __launch_bounds__(THREADS)
     } else if (last) {
       for (int i = tid; i < n; i += THREADS) {
         keys_out[off + i] = s_key[i];
-        pos_out[off + i] = int32_t(s_pos[i]);
+        pos_out[off + i] = base + int32_t(s_pos[i]);
       }
     } else {
 #pragma unroll
@@ -422,7 +426,7 @@ void launch_block_sort(const uint32_t* keys, const int32_t* vals, int64_t S, int
                        int t0, int t_hi, int chunk, uint32_t* keys_out, int32_t* pos_out, hipStream_t stream) {
 #define ZETA_BLOCK_SORT(THREADS, KPT)                                                                             \
   hipLaunchKernelGGL((block_sort_kernel<THREADS, KPT, kByLevel>), dim3(unsigned(S)), dim3(THREADS), 0, stream, keys, \
-                     vals, N, code_bits, digit_bits, t0, t_hi, chunk, keys_out, pos_out)
+                     vals, N, 1, code_bits, digit_bits, t0, t_hi, chunk, keys_out, pos_out)
   if (N <= 1024)
     ZETA_BLOCK_SORT(512, 2);
   else if (N <= 2048)
@@ -434,6 +438,53 @@ void launch_block_sort(const uint32_t* keys, const int32_t* vals, int64_t S, int
   else
     ZETA_BLOCK_SORT(1024, 16);
 #undef ZETA_BLOCK_SORT
+}
+
+// ---- sorted runs, merged ----------------------------------------------------------
+// A segment as up to kMergeRuns stretches of kMergeRun keys, each sorted by a
+// workgroup (block_sort), then merged in one launch: an element's place is its
+// index in its run plus, for every other run, the number of that run's
+// elements that come before it (those with a smaller code, and in an earlier
+// run, whose positions are all smaller, an equal one).  The searches of all
+// runs advance together, so their loads are in flight at once; consecutive
+// elements of a run search neighbouring places.
+// Bound: latency (13 dependent loads) when there are few elements, else the
+// searches' loads (merge_sort_path has the figures).
+constexpr int kMergeThreads = 256;
+
+__global__ void __launch_bounds__(kMergeThreads)
+    merge_runs_kernel(const uint32_t* __restrict__ run_keys, const int32_t* __restrict__ run_pos, int64_t N,
+                      int64_t blocks_per_seg, uint32_t* __restrict__ keys_out, int32_t* __restrict__ pos_out) {
+  const int64_t blk = xcd_contiguous_block(blockIdx.x, gridDim.x);
+  const int64_t seg = blk / blocks_per_seg;
+  const int e = int(blk - seg * blocks_per_seg) * kMergeThreads + int(threadIdx.x);
+  if (e >= N) return;
+  const uint32_t* ks = run_keys + seg * N;
+  const int n = int(N);
+  const int runs = (n + int(kMergeRun) - 1) / int(kMergeRun);
+  const int mine = e / int(kMergeRun);  // the same for the whole wavefront
+  const uint32_t key = ks[e];
+  const int32_t pos = run_pos[seg * N + e];
+  int lo[kMergeRuns];
+#pragma unroll
+  for (int r = 0; r < kMergeRuns; ++r) lo[r] = 0;
+  for (int step = int(kMergeRun); step >= 1; step >>= 1) {
+#pragma unroll
+    for (int r = 0; r < kMergeRuns; ++r) {
+      if (r < runs && r != mine) {
+        const int start = r * int(kMergeRun);
+        const int len = n - start < int(kMergeRun) ? n - start : int(kMergeRun);
+        const int at = lo[r] + step;
+        const uint32_t x = ks[start + (at <= len ? at : len) - 1];
+        if (at <= len && (x < key || (r < mine && x == key))) lo[r] = at;
+      }
+    }
+  }
+  int rank = e - mine * int(kMergeRun);
+#pragma unroll
+  for (int r = 0; r < kMergeRuns; ++r) rank += lo[r];
+  keys_out[seg * N + rank] = key;
+  pos_out[seg * N + rank] = pos;
 }
 
 // One pass over tiles of kRadixThreads * kChunks keys: hist, [scan,] scatter.
@@ -487,6 +538,19 @@ hipError_t launch_sort(const uint32_t* k_codes, int64_t S, int64_t N, int code_b
     return hipGetLastError();
   }
   const SortWs ws = sort_ws(S, N, code_bits);
+  if (merge_sort_path(S, N, plan.passes)) {
+    uint32_t* run_keys = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + ws.keys_off);
+    int32_t* run_pos = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + ws.pos_off);
+    const int64_t runs = ceil_div(N, kMergeRun);
+    static_assert(kMergeRun == 4096, "a run is one workgroup's keys");
+    hipLaunchKernelGGL((block_sort_kernel<1024, 4, false>), dim3(unsigned(S * runs)), dim3(1024), 0, stream, k_codes,
+                       static_cast<const int32_t*>(nullptr), N, int(runs), code_bits, plan.digit_bits, 0, 0, 0, run_keys,
+                       run_pos);
+    const int64_t bps = ceil_div(N, int64_t(kMergeThreads));
+    hipLaunchKernelGGL(merge_runs_kernel, dim3(unsigned(S * bps)), dim3(kMergeThreads), 0, stream, run_keys, run_pos, N,
+                       bps, sorted_codes, perm);
+    return hipGetLastError();
+  }
   char* wsb = static_cast<char*>(workspace);
   uint32_t* hist = reinterpret_cast<uint32_t*>(wsb + ws.hist_off);
   uint32_t* tmp_keys = reinterpret_cast<uint32_t*>(wsb + ws.keys_off);

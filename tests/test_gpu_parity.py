@@ -168,15 +168,16 @@ def test_sort_shapes(S, N, code_bits):
     assert np.array_equal(host(sc), esc)
 
 
-@pytest.mark.parametrize("N", [1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 16384, 16385])
+@pytest.mark.parametrize("N", [1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 12288, 16384, 16385, 32767, 32768, 32769])
 @pytest.mark.parametrize("S", [2, 100])
 def test_sort_and_order_workgroup_edges(N, S):
     """The last and first segment lengths of each workgroup size of the
-    whole-segment sort, and of the tiled passes: one to four passes, codes
+    whole-segment sort, of the merged runs (two to eight, whole and ragged) and
+    of the tiled passes: one to four passes, codes
     whose every bit is set (the value that pads a segment) and heavy
     duplicates; the level partition at the same lengths, in place too."""
-    if S > 2 and N < 8192:
-        pytest.skip("the number of segments decides beyond 8192 keys only")
+    if S > 2 and not 8192 <= N <= 16385:
+        pytest.skip("the number of segments decides between 8192 and 16384 keys only")
     log(f"sort and order edges N={N} S={S}")
     rng = np.random.default_rng(N)
     for code_bits in (1, 9, 18, 32) if S == 2 else (32,):

@@ -92,12 +92,13 @@ hipError_t launch_attend_idx_tile(const void* q, const void* k, const void* v, i
                                   const int32_t* idx, const int32_t* q_order, int score, float eps, HistMean hm,
                                   void* out, hipStream_t stream);
 // The tiles' inputs alone: key rows in list order (d_k = 3) and the window
-// bounds of every processing-order slot (idx_out optional).
+// bounds of every processing-order slot (idx_out optional), over the lists
+// built for list_topk (0: topk).
 hipError_t launch_tile_windows(const void* k, int64_t S, int64_t N, int dk, int topk, bool causal, int chunk,
                                const uint32_t* q_codes, const uint32_t* sorted_codes, const int32_t* perm,
                                const uint32_t* list_codes, const int32_t* list_pos, const int32_t* q_order,
                                int32_t* idx_out, int2* bounds, uint2* keys_full, uint2* keys_list,
-                               bool keys_built, hipStream_t stream);
+                               bool keys_built, hipStream_t stream, int list_topk = 0);
 hipError_t launch_select_attend_tile(const void* q, const void* k, const void* v, int64_t S, int64_t N, int dk, int dv,
                                      int topk, bool causal, int chunk, const uint32_t* q_codes,
                                      const uint32_t* sorted_codes,

@@ -1561,8 +1561,8 @@ hipError_t launch_tile_windows(const void* k, int64_t S, int64_t N, int dk, int 
                                const uint32_t* q_codes, const uint32_t* sorted_codes, const int32_t* perm,
                                const uint32_t* list_codes, const int32_t* list_pos, const int32_t* q_order,
                                int32_t* idx_out, int2* bounds, uint2* keys_full, uint2* keys_list, bool keys_built,
-                               hipStream_t stream) {
-  const ListPlan lp = list_plan(N, topk);
+                               hipStream_t stream, int list_topk) {
+  const ListPlan lp = list_plan(N, list_topk > 0 ? list_topk : topk);
   const int64_t total = S * N;
   if (dk == 3 && !keys_built) {
     // Prefix lists exist only for causal calls with levels.

@@ -776,16 +776,23 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
     uint4 st = make_uint4(0u, 0u, 0u, 0u);
     auto load_rec = [&](int32_t tau) { st = reinterpret_cast<const uint4*>(rseg + tau * 16)[lane & 31]; };
     // The loaded records into buffer `buf` (a query of another list, or past
-    // the segment's end, gets the empty window and position 0), and their dout
-    // rows' copies issued (weight 0 where the window is empty).
+    // the segment's end, gets the empty window), and their dout rows' copies
+    // issued.  A row of weight 0 still enters the products, where an infinity
+    // or NaN would not vanish: the place of a query without a window here
+    // takes the row of the tile's first query with one, never some other row.
     auto stage = [&](int32_t tau, int buf) {
       const uint32_t list = uint32_t(__builtin_amdgcn_update_dpp(int(st.y), int(st.y), 0xB1, 0xF, 0xF, false)) >> 16;  // the pair's other lane
       const bool past = tau * 16 + ((lane & 31) >> 1) >= n32;
       if (past) st = make_uint4(0u, 0u, 0u, 0u);
-      if ((lane & 1) != 0 && (past || list != li)) {
+      const bool other = past || list != li;
+      // A visited tile has a window in this list, so such a lane exists.
+      const uint64_t own = wave_ballot((lane & 1) != 0 && !other);
+      const uint32_t own_row = uint32_t(
+          __builtin_amdgcn_readlane(int(st.w), own != 0ull ? __ffsll((unsigned long long)own) - 1 : 0));
+      if ((lane & 1) != 0 && other) {
         st.x = uint32_t(INT32_MIN);
         st.y = 0u;
-        st.w = 0u;
+        st.w = own != 0ull ? own_row : 0u;
       }
       if (lane < 32) *reinterpret_cast<uint4*>(&s_rec[wave][buf][lane >> 1][(lane & 1) * 4]) = st;
 #pragma unroll

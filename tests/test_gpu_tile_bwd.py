@@ -126,6 +126,29 @@ def test_tile_bwd_tile_counts(N):
     _check(idx, got, f, oracle.as_f32(dout_raw, w.dtype), 0.5)
 
 
+@pytest.mark.parametrize("dv", [32, 128])
+def test_tile_bwd_nan_without_window(dv):
+    """The chunked rule leaves the first chunk's queries without a window:
+    whatever their dout rows hold (here NaN and infinities, the first row's
+    among them), no gradient changes, also where an order mixes them and
+    several lists in one tile."""
+    w = workloads.custom(B=1, H=2, N=1000, dv=dv, topk=16, dtype="bf16", bits=8, seed=dv)
+    log(f"tile bwd NaN dout without window dv={dv}")
+    raw = {n: a.reshape(2, w.N, -1) for n, a in workloads.generate(w).items()}
+    clean = workloads.generate_dout(w).reshape(2, w.N, dv).copy()
+    clean[:, :100] = 0
+    dirty = clean.copy()
+    dirty[:, :100:3] = np.array(0x7FC0).astype(dirty.dtype)
+    dirty[:, 1:100:3] = np.array(0x7F80).astype(dirty.dtype)
+    rng = np.random.default_rng(dv)
+    perm = np.stack([rng.permutation(w.N) for _ in range(2)]).astype(np.int32)
+    for order in ("level", "position", perm):
+        want = _gpu(raw, clean, w, True, 0.5, chunk=100, order=order)
+        got = _gpu(raw, dirty, w, True, 0.5, chunk=100, order=order)
+        for a, b in zip(got, want):
+            assert np.array_equal(a, b)
+
+
 def test_tile_bwd_orders_and_repeat():
     """Any processing order gives the oracle's gradients; dq and deps's parts
     depend only on each query's own window, so dq is bit-identical across

@@ -353,11 +353,11 @@ __global__ void __launch_bounds__(THREADS)
   float lo[3], hi[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    lo[a] = fminf(xq[a], xk[a]);
-    hi[a] = fmaxf(xq[a], xk[a]);
+    lo[a] = __builtin_huge_valf();  // an axis of NaN alone keeps these
+    hi[a] = -__builtin_huge_valf();
   }
 #pragma unroll
-  for (int i = 3; i < 24; ++i) {
+  for (int i = 0; i < 24; ++i) {
     lo[i % 3] = fminf(lo[i % 3], fminf(xq[i], xk[i]));
     hi[i % 3] = fmaxf(hi[i % 3], fmaxf(xq[i], xk[i]));
   }

@@ -129,6 +129,25 @@ def test_encode_workgroup_edges(N, dtype):
         assert np.array_equal(host(rng_out), np.stack([lo, hi], axis=1))
 
 
+@pytest.mark.parametrize("N", [5, 300, 5000])
+def test_encode_nan_axis(N):
+    """An axis that holds only NaN has the empty range (+inf, -inf) and cell 0
+    whatever the length's kernel; NaN elsewhere is left out of the range."""
+    log(f"encode NaN axis N={N}")
+    rng = np.random.default_rng(N)
+    q, k = (rng.standard_normal((1, 2, N, 3)).astype(np.float32) for _ in range(2))
+    q[..., 1] = k[..., 1] = np.nan
+    q[0, 0, 0, 0] = np.nan
+    out = torch.empty((2, 2, 3), dtype=torch.float32, device="cuda:0")
+    qc, kc = zeta.zeta_morton_encode(to_dev(q, "f32"), to_dev(k, "f32"), 10, range_out=out)
+    torch.cuda.synchronize()
+    both = np.concatenate([q, k], axis=2)[0]
+    lo, hi = np.fmin.reduce(both, axis=1), np.fmax.reduce(both, axis=1)
+    lo[:, 1], hi[:, 1] = np.inf, -np.inf
+    assert np.array_equal(host(out), np.stack([lo, hi], axis=1))
+    assert not (host(qc).astype(np.int64) & 0x12492492).any() and not (host(kc).astype(np.int64) & 0x12492492).any()
+
+
 def test_encode_constant_inputs():
     """hi == lo on every axis: every code is 0."""
     q = np.full((1, 2, 77, 3), 0.25, dtype=np.float32)

@@ -170,7 +170,9 @@ __global__ void __launch_bounds__(kKnnWaves * 64)
   for (int r = 0; r < M; ++r) {
     const int j = r * 64 + lane;
     const int jc = j < end ? j : end - 1;
-    d[r] = __float_as_int(plain_d2<T, KD>(qv, kseg + int64_t(jc) * dk, dk));
+    // A NaN, of either sign, is above infinity and below "no key".
+    const uint32_t bits = __float_as_uint(plain_d2<T, KD>(qv, kseg + int64_t(jc) * dk, dk));
+    d[r] = int(bits < uint32_t(kKnnNone) ? bits : uint32_t(kKnnNone) - 1u);
   }
 #pragma unroll
   for (int r = 0; r < M; ++r) {

@@ -65,6 +65,24 @@ def test_exact_knn_ties(N, kn, causal):
     assert np.array_equal(got[:, rows], want)
 
 
+@pytest.mark.parametrize("N,kn", [(200, 64), (2048, 64), (500, 65)])
+def test_exact_knn_nan(N, kn):
+    """Keys with a NaN of either sign or payload come after every other key,
+    infinitely far ones included."""
+    log(f"exact knn NaN N={N} kn={kn}")
+    rng = np.random.default_rng([N, kn])
+    q, k = (rng.standard_normal((1, 1, N, 3)).astype(np.float32) for _ in range(2))
+    bad = np.sort(rng.permutation(N)[:N - kn])
+    nan = np.array([0x7FC00000, 0xFFC00000, 0x7FFFFFFF, 0xFFFFFFFF], np.uint32).view(np.float32)
+    k[0, 0, bad, 1] = nan[np.arange(len(bad)) % 4]
+    k[0, 0, np.setdiff1d(np.arange(N), bad)[:9], 2] = np.inf
+    got = host(zeta.zeta_exact_knn(to_dev(q, "f32"), to_dev(k, "f32"), kn, False)).reshape(N, kn)
+    assert not np.isin(got, bad).any()
+    want = np.setdiff1d(np.arange(N), bad)
+    assert np.array_equal(np.sort(got, axis=1), np.tile(want, (N, 1)))
+    assert np.isinf(k[0, 0, got[:, -9:], 2]).all()
+
+
 def test_index_overlap():
     log("index overlap")
     rng = np.random.default_rng(3)

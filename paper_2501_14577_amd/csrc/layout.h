@@ -298,7 +298,7 @@ inline QueryOrderWs query_order_ws(int64_t S, int64_t N) {
 // deps and, with the history-mean candidate, the gradients reaching the means
 // and their scan's sums.
 constexpr int64_t kTileBwdRedPer = 4096;  // deps parts per block sum (at least)
-constexpr int64_t kTileBwdRedMax = 1024;  // block sums at most
+constexpr int64_t kTileBwdRedMax = 512;  // block sums (64-bit) at most
 // The gradients' own prefix lists start up to two levels later than the
 // forward's, as long as the first holds at most an eighth of the keys: the
 // queries of the levels left out search a longer list (a few percent more
@@ -330,7 +330,7 @@ inline TileBwdWs tile_bwd_ws(int64_t S, int64_t N, int dv, int topk, int causal,
   w.env2_off = w.env_off + align_up(env);
   w.ranges_off = w.env2_off + align_up(env);
   w.sums_off = w.ranges_off + align_up(env);
-  w.hist_k_off = w.sums_off + align_up(size_t(kTileBwdRedMax) * sizeof(float));
+  w.hist_k_off = w.sums_off + align_up(size_t(kTileBwdRedMax) * sizeof(double));
   w.hist_v_off = w.hist_k_off;
   w.hist_scan_off = w.hist_k_off;
   w.bytes = w.hist_k_off;

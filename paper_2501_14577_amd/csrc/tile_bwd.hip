@@ -453,9 +453,10 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
     }
     if (lane < nl) env[(int64_t(lane) * S + seg) * ct + tau] = my_env;
     // The tile's part of deps: lanes 0..15 hold the queries', summed as a tree.
+    double tile_deps = my_deps;
 #pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) my_deps += __shfl_xor(my_deps, off, 64);
-    if (lane == 0) deps_part[tile] = my_deps;
+    for (int off = 8; off >= 1; off >>= 1) tile_deps += __shfl_xor(tile_deps, off, 64);
+    if (lane == 0) deps_part[tile] = float(tile_deps);
   }
 }
 
@@ -934,26 +935,30 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
 
 // ---- deps -----------------------------------------------------------------------
 // Fixed-order sum of the tiles' parts: one block when there are at most
-// kRedOne of them, else block sums first and then one block over those.
+// kRedOne of them, else block sums first and then one block over those.  Sums
+// are kept in 64 bits: the parts' signs differ, so the sum is smaller than what
+// it adds up and would show every rounding of 32 bits (the loads bound the
+// kernel either way).
 constexpr int64_t kRedOne = int64_t(1) << 17;
 
+template <typename In, typename Out>
 __global__ void __launch_bounds__(kRedThreads)
-    bwd_tile_reduce_kernel(const float* __restrict__ part, int64_t n, int64_t per_block, float* __restrict__ sums) {
-  __shared__ float s_red[kRedThreads];
+    bwd_tile_reduce_kernel(const In* __restrict__ part, int64_t n, int64_t per_block, Out* __restrict__ sums) {
+  __shared__ double s_red[kRedThreads];
   const int64_t b0 = int64_t(blockIdx.x) * per_block;
   const int64_t b1 = b0 + per_block < n ? b0 + per_block : n;
   // Independent loads in batches, so their latencies overlap.
   constexpr int kBatch = 16;
-  float acc = 0.0f;
+  double acc = 0.0;
   for (int64_t t = b0 + threadIdx.x; t < b1; t += kBatch * kRedThreads) {
-    float x[kBatch];
+    In x[kBatch];
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
       const int64_t e = t + j * kRedThreads;
       x[j] = part[e < b1 ? e : t];
     }
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) acc += t + j * kRedThreads < b1 ? x[j] : 0.0f;
+    for (int j = 0; j < kBatch; ++j) acc += t + j * kRedThreads < b1 ? double(x[j]) : 0.0;
   }
   s_red[threadIdx.x] = acc;
   __syncthreads();
@@ -961,7 +966,7 @@ __global__ void __launch_bounds__(kRedThreads)
     if (int(threadIdx.x) < w) s_red[threadIdx.x] += s_red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) sums[blockIdx.x] = s_red[0];
+  if (threadIdx.x == 0) sums[blockIdx.x] = Out(s_red[0]);
 }
 
 template <int DV>
@@ -981,7 +986,7 @@ hipError_t launch_tile_bwd_t(const uint16_t* q, const uint16_t* v, const uint16_
   int2* ranges = reinterpret_cast<int2*>(wsb + ws.ranges_off);
   float* hk = reinterpret_cast<float*>(wsb + ws.hist_k_off);
   float* hv = reinterpret_cast<float*>(wsb + ws.hist_v_off);
-  float* sums = reinterpret_cast<float*>(wsb + ws.sums_off);
+  double* sums = reinterpret_cast<double*>(wsb + ws.sums_off);
   const int64_t nenv = int64_t(nl) * S * ct;
   const int cz = causal ? 1 : 0;
   {
@@ -1062,15 +1067,17 @@ hipError_t launch_tile_bwd_t(const uint16_t* q, const uint16_t* v, const uint16_
   }
   const int64_t total = S * ct;
   if (total <= kRedOne) {
-    hipLaunchKernelGGL(bwd_tile_reduce_kernel, dim3(1), dim3(kRedThreads), 0, stream, part, total, total, deps);
+    hipLaunchKernelGGL((bwd_tile_reduce_kernel<float, float>), dim3(1), dim3(kRedThreads), 0, stream, part, total, total,
+                       deps);
     return hipGetLastError();
   }
   const int64_t nred = ceil_div(total, kTileBwdRedPer) < kTileBwdRedMax ? ceil_div(total, kTileBwdRedPer)
                                                                         : kTileBwdRedMax;
   const int64_t per = ceil_div(total, nred);
-  hipLaunchKernelGGL(bwd_tile_reduce_kernel, dim3(unsigned(nred)), dim3(kRedThreads), 0, stream, part, total, per,
-                     sums);
-  hipLaunchKernelGGL(bwd_tile_reduce_kernel, dim3(1), dim3(kRedThreads), 0, stream, sums, nred, nred, deps);
+  hipLaunchKernelGGL((bwd_tile_reduce_kernel<float, double>), dim3(unsigned(nred)), dim3(kRedThreads), 0, stream, part,
+                     total, per, sums);
+  hipLaunchKernelGGL((bwd_tile_reduce_kernel<double, float>), dim3(1), dim3(kRedThreads), 0, stream, sums, nred, nred,
+                     deps);
   return hipGetLastError();
 }
 

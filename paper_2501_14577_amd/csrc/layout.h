@@ -339,6 +339,9 @@ inline TileBwdWs tile_bwd_ws(int64_t S, int64_t N, int dv, int topk, int causal,
     w.hist_scan_off = w.hist_v_off + align_up(rows * size_t(dv) * sizeof(float));
     w.bytes = w.hist_scan_off + hist_ws(S, N, 3 + dv).bytes;
   }
+  // The size callers know for this call also holds a copy of the dout rows;
+  // that room is unused since the key pass gathers the rows itself.
+  w.bytes += align_up(rows * size_t(dv) * 2);
   return w;
 }
 

@@ -57,10 +57,12 @@ namespace {
 constexpr int kBtWaves = 4;          // wavefronts per block
 constexpr int kBtChunk = kChunk;      // list entries per product step
 constexpr int kRedThreads = 1024;
-constexpr uint32_t kNoList = 0xFFFFu;  // record of a slot whose query has no window
+constexpr uint32_t kNoList = 0x7FFFu;    // list index of a slot whose query has no window
+constexpr uint32_t kNonFinite = 0x8000u;  // beside the list index: weight 0 times this query's terms may be NaN
 
 // What the key pass needs of a slot's query, in 32 bytes: q as bfloat16 bits,
-// the list index (kNoList: no window), 1/Z, c, the window as its first list
+// the list index (kNoList: no window; with kNonFinite when q, or dout or a
+// value row by way of c, is not finite), 1/Z, c, the window as its first list
 // index a and its last less a (no window: a = INT32_MIN, span = 0, which no
 // entry meets), the pool limit and the query's position.
 struct alignas(16) SlotRec {
@@ -440,7 +442,12 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
         my_deps = -inv * (xz - cc * yz);
         SlotRec r;
         r.q01 = (__float_as_uint(qv[0]) >> 16) | (__float_as_uint(qv[1]) & 0xFFFF0000u);
-        const uint32_t list = mine ? uint32_t(level_index(g_lvl, causal, t0, t_hi, levels)) : kNoList;
+        uint32_t list = mine ? uint32_t(level_index(g_lvl, causal, t0, t_hi, levels)) : kNoList;
+        // An infinite or NaN element of dout makes every dot product and so c
+        // infinite or NaN.
+        const bool finite = __builtin_isfinite(cc) && __builtin_isfinite(qv[0]) && __builtin_isfinite(qv[1]) &&
+                            __builtin_isfinite(qv[2]);
+        list |= finite ? 0u : kNonFinite;
         r.q2_list = (__float_as_uint(qv[2]) >> 16) | (list << 16);
         r.zinv = inv;
         r.c = cc;
@@ -750,24 +757,23 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
     const SlotRec* rseg = rec + seg * N;
     const unsigned char* dbytes = reinterpret_cast<const unsigned char*>(dout + seg * N * DV);
 
-    // The tiles whose windows meet the chunks, 64 candidates tested at once.
+    // The tiles whose windows meet the chunks, 64 candidates tested at once;
+    // `every`: the tile returned meets every chunk, not some only.
     int64_t blk_base = ta, cur_base = ta;
-    uint64_t pend = 0ull;
-    auto next_tile = [&]() -> int32_t {
+    uint64_t pend = 0ull, in_every = 0ull;
+    auto next_tile = [&](bool& every) -> int32_t {
       while (pend == 0ull && blk_base < tb) {
         const int64_t tl = blk_base + lane;
-        bool hit = false;
-        if (tl < tb) {
-          const int2 rg = ev[tl];
-          hit = (rg.x <= hi_c) & (rg.y >= lo_c);
-        }
-        pend = wave_ballot(hit);
+        const int2 rg = tl < tb ? ev[tl] : make_int2(INT32_MAX, INT32_MIN);
+        pend = wave_ballot((rg.x <= hi_c) & (rg.y >= lo_c));
+        if (SUB > 1) in_every = wave_ballot((rg.x < lo_c + kBtChunk) & (rg.y >= lo_c + (SUB - 1) * kBtChunk));
         cur_base = blk_base;
         blk_base += 64;
       }
       if (pend == 0ull) return -1;
       const int b = __ffsll((unsigned long long)pend) - 1;
       pend &= pend - 1ull;
+      every = SUB == 1 || ((in_every >> b) & 1ull) != 0ull;
       return int32_t(cur_base) + b;
     };
     // Half a record per lane (lanes 0..31; the others repeat them): q, list,
@@ -781,11 +787,12 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
     // issued.  A row of weight 0 still enters the products, where an infinity
     // or NaN would not vanish: the place of a query without a window here
     // takes the row of the tile's first query with one, never some other row.
-    auto stage = [&](int32_t tau, int buf) {
+    // Returns whether a query of this list is not finite.
+    auto stage = [&](int32_t tau, int buf) -> bool {
       const uint32_t list = uint32_t(__builtin_amdgcn_update_dpp(int(st.y), int(st.y), 0xB1, 0xF, 0xF, false)) >> 16;  // the pair's other lane
       const bool past = tau * 16 + ((lane & 31) >> 1) >= n32;
       if (past) st = make_uint4(0u, 0u, 0u, 0u);
-      const bool other = past || list != li;
+      const bool other = past || (list & ~kNonFinite) != li;
       // A visited tile has a window in this list, so such a lane exists.
       const uint64_t own = wave_ballot((lane & 1) != 0 && !other);
       const uint32_t own_row = uint32_t(
@@ -804,6 +811,7 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
                                          (__attribute__((address_space(3))) void*)(s_d[wave] + buf * VS::kBytes + 1024 * j),
                                          16, 0, 0);
       }
+      return (wave_ballot(list >= kNonFinite) & own) != 0ull;
     };
     // The rows' fragments of buffer `buf`, as they lie and transposed (read
     // twice, once per K half of the products).
@@ -820,12 +828,13 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
         tr[2 * j + 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(at);
       }
     };
-    auto sum_tile = [&](int buf) {
+    // The tile in buffer `buf` into chunks U0 .. U1 - 1.
+    auto sum_chunks = [&](int buf, auto U0, auto U1) {
       // Dot products: lane holds p for queries 4kg..4kg+3 and entry ent of each
       // chunk (A rows: dout of the tile's query ent).
       f32x4_t d[SUB];
 #pragma unroll
-      for (int u = 0; u < SUB; ++u) {
+      for (int u = U0; u < U1; ++u) {
         d[u] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int s = 0; s < NS; ++s)
@@ -841,7 +850,7 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
         const float qz = __uint_as_float(h0.y << 16);
         const float zinv = __uint_as_float(h0.z), cc = __uint_as_float(h0.w);
 #pragma unroll
-        for (int u = 0; u < SUB; ++u) {
+        for (int u = U0; u < U1; ++u) {
           const float df[3] = {qx - kv[u][0], qy - kv[u][1], qz - kv[u][2]};
           const float d2 = fmaf(df[2], df[2], fmaf(df[1], df[1], fmaf(df[0], df[0], eps)));
           const bool in = (uint32_t(e[u]) - h1.x <= h1.y) & (uint32_t(pos_e[u]) <= h1.z);
@@ -857,7 +866,7 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
       // same dout fragment).
       Frag8 b[SUB];
 #pragma unroll
-      for (int u = 0; u < SUB; ++u) {
+      for (int u = U0; u < U1; ++u) {
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
           const bf16x2_t h = {(__bf16)aw[u][2 * t], (__bf16)aw[u][2 * t + 1]};
@@ -873,15 +882,20 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
       for (int j = 0; j < E; ++j) {
         const bf16x8_t a8 = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(tr[2 * j], tr[2 * j + 1], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-        for (int u = 0; u < SUB; ++u) acc[u][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, b[u].v, acc[u][j], 0, 0, 0);
+        for (int u = U0; u < U1; ++u) acc[u][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, b[u].v, acc[u][j], 0, 0, 0);
       }
     };
-    const int32_t head = next_tile();
+    using std::integral_constant;
+    using AllChunks = integral_constant<int, SUB>;
+    bool every = true, deferred = false;
+    const int32_t head = next_tile(every);
     const bool touched = head >= 0;
     if (touched) {
       load_rec(head);
-      stage(head, 0);
-      int32_t nxt = next_tile();
+      // Weight 0 times a term that is not finite is NaN: a tile that holds one
+      // must not enter a chunk it does not meet, and is left for below.
+      bool leave = stage(head, 0) && !every;
+      int32_t nxt = next_tile(every);
       if (nxt >= 0) load_rec(nxt);
       // The tile in buffer `buf` is read whole first; then the next tile's
       // copies into the other buffer are issued and the records of the one
@@ -890,15 +904,40 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
       for (int buf = 0;; buf ^= 1) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this tile's rows (and the next one's records) have landed
         read_tile(buf);
-        const bool more = nxt >= 0;
+        const bool more = nxt >= 0, skip = leave;
         if (more) {
-          stage(nxt, buf ^ 1);
-          nxt = next_tile();
+          leave = stage(nxt, buf ^ 1) && !every;
+          nxt = next_tile(every);
           if (nxt >= 0) load_rec(nxt);
         }
         wave_lds_sync();
-        sum_tile(buf);
+        if (skip)
+          deferred = true;
+        else
+          sum_chunks(buf, integral_constant<int, 0>{}, AllChunks{});
         if (!more) break;
+      }
+    }
+    if constexpr (SUB > 1) {
+      static_assert(SUB == 2, "a tile meets both chunks or one");
+      // The tiles left out above, each into the one chunk it meets.
+      if (deferred) {
+        blk_base = ta;
+        for (int32_t t = next_tile(every); t >= 0; t = next_tile(every)) {
+          if (every) continue;
+          load_rec(t);
+          const bool nonfinite = stage(t, 0);
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          wave_lds_sync();
+          if (nonfinite) {
+            read_tile(0);
+            if (__builtin_amdgcn_readfirstlane(ev[t].y) < lo_c + kBtChunk)
+              sum_chunks(0, integral_constant<int, 0>{}, integral_constant<int, 1>{});
+            else
+              sum_chunks(0, integral_constant<int, 1>{}, integral_constant<int, 2>{});
+          }
+          wave_lds_sync();
+        }
       }
     }
 

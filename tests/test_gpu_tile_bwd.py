@@ -149,6 +149,44 @@ def test_tile_bwd_nan_without_window(dv):
             assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("dv", [64, 128])
+def test_tile_bwd_nonfinite_row_stays_in_its_chunks(dv):
+    """A NaN or infinite dout row of a query with a window reaches the keys of
+    the 16-entry chunks that its tile's windows meet, and no others: every key
+    outside them has the bits it has with that row zero.  Enough rows that a
+    wavefront of the key pass takes two chunks, an odd number of them."""
+    w = workloads.custom(B=1, H=8, N=4112, dv=dv, topk=16, dtype="bf16", bits=8, seed=dv + 5)
+    log(f"tile bwd non-finite dout row dv={dv}")
+    S, N = w.segments, w.N
+    q, k, v = (to_dev(a.reshape(1, S, N, -1), w.dtype) for a in workloads.generate(w).values())
+    res = zeta.forward(q, k, v, w.topk, 0.5, False, w.bits, fused=True, return_intermediates=True)
+    order, perm = (host(res[n]).reshape(S, N) for n in ("q_order", "perm"))
+    idx = host(res["idx"]).reshape(S, N, w.topk)
+    seg = np.arange(S)
+    slot = np.random.default_rng(dv).integers(0, N, S)
+    dirty_q = order[seg, slot]
+    clean = workloads.generate_dout(w).reshape(S, N, dv).copy()
+    clean[seg, dirty_q] = 0
+    dirty = clean.copy()
+    dirty[seg, dirty_q] = np.where(seg % 2, 0x7FC0, 0x7F80)[:, None].astype(dirty.dtype)
+
+    def grads(dout):
+        g = zeta.zeta_select_attend_bwd(q, k, v, res["q_codes"], res["sorted_codes"], res["perm"], w.topk, False, 0.5,
+                                        to_dev(dout[None], w.dtype), q_order=res["q_order"])
+        torch.cuda.synchronize()
+        return [host(t).reshape(S, N, -1) for t in g[:3]]
+
+    (_, ck, cv), (_, gk, gv) = grads(clean), grads(dirty)
+    for s in range(S):
+        rank = np.empty(N, np.int64)
+        rank[perm[s]] = np.arange(N)
+        tile = order[s, slot[s] // 16 * 16:slot[s] // 16 * 16 + 16]
+        chunks = rank[idx[s, tile]] // 16
+        away = (rank // 16 < chunks.min()) | (rank // 16 > chunks.max())
+        assert np.array_equal(gk[s, away], ck[s, away]) and np.array_equal(gv[s, away], cv[s, away]), s
+        assert not np.isfinite(gv[s, idx[s, dirty_q[s]]]).any()
+
+
 def test_tile_bwd_orders_and_repeat():
     """Any processing order gives the oracle's gradients; dq and deps's parts
     depend only on each query's own window, so dq is bit-identical across

@@ -784,12 +784,13 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
     auto load_rec = [&](int32_t tau) { st = reinterpret_cast<const uint4*>(rseg + tau * 16)[lane & 31]; };
     // The loaded records into buffer `buf` (a query of another list, or past
     // the segment's end, gets the empty window), and their dout rows' copies
-    // issued.  A row of weight 0 still enters the products, where an infinity
-    // or NaN would not vanish: the place of a query without a window here
-    // takes the row of the tile's first query with one, never some other row.
+    // issued.  A query of weight 0 still enters the products and sums, where an
+    // infinity or NaN would not vanish: one without a window here has q, 1/Z and
+    // c zero and takes the row of the tile's first query with one.
     // Returns whether a query of this list is not finite.
     auto stage = [&](int32_t tau, int buf) -> bool {
-      const uint32_t list = uint32_t(__builtin_amdgcn_update_dpp(int(st.y), int(st.y), 0xB1, 0xF, 0xF, false)) >> 16;  // the pair's other lane
+      const uint32_t pair = uint32_t(__builtin_amdgcn_update_dpp(int(st.y), int(st.y), 0xB1, 0xF, 0xF, false));
+      const uint32_t list = ((lane & 1) != 0 ? pair : st.y) >> 16;  // held by the even lane
       const bool past = tau * 16 + ((lane & 31) >> 1) >= n32;
       if (past) st = make_uint4(0u, 0u, 0u, 0u);
       const bool other = past || (list & ~kNonFinite) != li;
@@ -797,10 +798,12 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
       const uint64_t own = wave_ballot((lane & 1) != 0 && !other);
       const uint32_t own_row = uint32_t(
           __builtin_amdgcn_readlane(int(st.w), own != 0ull ? __ffsll((unsigned long long)own) - 1 : 0));
-      if ((lane & 1) != 0 && other) {
-        st.x = uint32_t(INT32_MIN);
+      if (other) {
+        const bool odd = (lane & 1) != 0;
+        st.x = odd ? uint32_t(INT32_MIN) : 0u;
         st.y = 0u;
-        st.w = own != 0ull ? own_row : 0u;
+        st.z = odd ? st.z : 0u;
+        st.w = odd && own != 0ull ? own_row : 0u;
       }
       if (lane < 32) *reinterpret_cast<uint4*>(&s_rec[wave][buf][lane >> 1][(lane & 1) * 4]) = st;
 #pragma unroll

@@ -187,6 +187,30 @@ def test_tile_bwd_nonfinite_row_stays_in_its_chunks(dv):
         assert not np.isfinite(gv[s, idx[s, dirty_q[s]]]).any()
 
 
+@pytest.mark.parametrize("N,H,dv", [(1000, 2, 32), (4112, 8, 64)])
+def test_tile_bwd_nonfinite_row_stays_in_its_list(N, H, dv):
+    """A non-finite dout row of a query that searches a short prefix list
+    changes no key outside that list, also where an order mixes queries of
+    several lists in one tile: the dirty queries lie among the first 60
+    positions, whose list holds the positions below 64 (or fewer)."""
+    w = workloads.custom(B=1, H=H, N=N, dv=dv, topk=16, dtype="bf16", bits=8, seed=dv + 6)
+    log(f"tile bwd non-finite dout row of another list N={N} dv={dv}")
+    raw = {n: a.reshape(H, N, -1) for n, a in workloads.generate(w).items()}
+    clean = workloads.generate_dout(w).reshape(H, N, dv).copy()
+    clean[:, 3:60:7] = 0
+    dirty = clean.copy()
+    dirty[:, 3:60:14] = np.array(0x7FC0).astype(dirty.dtype)
+    dirty[:, 10:60:14] = np.array(0x7F80).astype(dirty.dtype)
+    others = np.setdiff1d(np.arange(N), np.arange(3, 60, 7))
+    rng = np.random.default_rng(N)
+    perm = np.stack([rng.permutation(N) for _ in range(H)]).astype(np.int32)
+    for order in ("level", "position", perm):
+        _, cq, ck, cv, _ = _gpu(raw, clean, w, True, 0.5, order=order)
+        _, gq, gk, gv, _ = _gpu(raw, dirty, w, True, 0.5, order=order)
+        assert np.array_equal(gq[:, others], cq[:, others])
+        assert np.array_equal(gk[:, 64:], ck[:, 64:]) and np.array_equal(gv[:, 64:], cv[:, 64:])
+
+
 def test_tile_bwd_orders_and_repeat():
     """Any processing order gives the oracle's gradients; dq and deps's parts
     depend only on each query's own window, so dq is bit-identical across

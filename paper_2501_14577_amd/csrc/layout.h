@@ -68,6 +68,9 @@ inline bool merge_sort_path(int64_t S, int64_t N, int passes) {
 
 // ---- select ---------------------------------------------------------------
 constexpr int kMaxLevels = 32;
+// List entries the window search stages in LDS for a run of queries; a shorter
+// list is staged whole.
+constexpr int kBndRegion = 640;
 // Up to this many keys per segment a prefix-list tile counts the earlier tiles'
 // entries itself.
 constexpr int64_t kListInline = 4096;
@@ -102,7 +105,9 @@ inline SortPlan sort_plan(int64_t N, int code_bits) {
 // segment's region of `cap` entries.  A query at position i reads
 // F_{max(t0, bitlen(i))} when that level exists and the full sorted list
 // otherwise; either list contains its whole causal pool and at least half of
-// the list's entries belong to the pool (or the list has under 2*topk entries).
+// the list's entries belong to the pool (or it is the first list, which has
+// under 2*topk entries for the topk it is planned for: the gradients plan for a
+// larger one than their windows').
 struct ListPlan {
   int t0;
   int t_hi;
@@ -300,13 +305,17 @@ inline QueryOrderWs query_order_ws(int64_t S, int64_t N) {
 constexpr int64_t kTileBwdRedPer = 4096;  // deps parts per block sum (at least)
 constexpr int64_t kTileBwdRedMax = 512;  // block sums (64-bit) at most
 // The gradients' own prefix lists start up to two levels later than the
-// forward's, as long as the first holds at most an eighth of the keys: the
-// queries of the levels left out search a longer list (a few percent more
-// chunks), and the key pass saves a launch of 8-17 us for each.
+// forward's, as long as the first holds at most an eighth of the keys and the
+// window search stages it whole: the queries of the levels left out search a
+// longer list, in which as little as one entry may be in their pool (a few
+// percent more chunks), and the key pass saves a launch of 8-17 us for each.  A
+// first list too long to stage is scanned from memory there and costs more
+// than the launches saved: with it -> without, d_v 64, 16 x 16384, k 300 676 -> 473 us,
+// k 512 890 -> 686; 1 x 65536, k 1024 1045 -> 716.
 inline int tile_bwd_list_topk(int64_t N, int topk) {
   const int t0 = ceil_log2(topk);
   int t = t0;
-  while (t < t0 + 2 && (int64_t(1) << (t + 4)) <= N) ++t;
+  while (t < t0 + 2 && (int64_t(1) << (t + 4)) <= N && (2 << t) <= kBndRegion) ++t;
   return t > t0 ? 1 << t : topk;
 }
 inline int tile_bwd_levels(int64_t N, int topk, bool causal) {

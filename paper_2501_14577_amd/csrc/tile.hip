@@ -114,7 +114,7 @@ constexpr uint32_t kIdxEmpty = 0xFFFFFFFFu;
 // keys, 128 x 4096, k 64, not causal: 46 -> 25 us; runs of one list, 16 x 65536,
 // k 128: 42 us either way).
 constexpr int kBndWaves = 4;
-constexpr int kRegion = 640;   // list entries staged per wavefront (a multiple of 64; 512 left more runs a second round)
+constexpr int kRegion = kBndRegion;  // list entries staged per wavefront (a multiple of 64; 512 left more runs a second round)
 constexpr int kMargin = 192;    // at most this many of them before the leading insertion point
 
 // Each wavefront's copy of a list range, in LDS.  Declared at file scope and
@@ -344,7 +344,7 @@ __global__ void __launch_bounds__(kBndWaves * 64)
     // windows are too long for a stretch to hold, the rest join it: they search
     // their lists in memory, all at once, and scan there what is not staged.
     const bool fits = topk <= kMargin - kScanStep;
-    const int32_t reach = fits ? topk : 0;  // at least every second entry of a prefix list is in the pool
+    const int32_t reach = fits ? topk : 0;  // in a list too long to stage whole, at least every second entry is in the pool
     const int32_t before = fits ? reach + kScanStep : kMargin;
     for (uint64_t pend = vmask; pend != 0ull;) {
       bool go = valid && ((pend >> lane) & 1ull) != 0ull;
@@ -355,7 +355,9 @@ __global__ void __launch_bounds__(kBndWaves * 64)
       const int32_t g_n = __builtin_amdgcn_readlane(Lq.n, leader);
       const uint32_t g_key = uint32_t(__builtin_amdgcn_readlane(int32_t(key), leader));
       const int32_t p0 = wave_lower_bound(g_codes, 0, g_n, g_key, lane);
-      const int32_t r0 = (p0 - before > 0 ? p0 - before : 0) & ~(kScanStep - 1);
+      // A short list is staged whole: its pools may be sparse, and a scan then
+      // runs far.
+      const int32_t r0 = g_n <= kRegion || p0 <= before ? 0 : (p0 - before) & ~(kScanStep - 1);
       const int32_t r1 = r0 + kRegion < g_n ? r0 + kRegion : g_n;
       {
         uint32_t cv[kRegion / 64];

@@ -126,6 +126,22 @@ def test_tile_bwd_tile_counts(N):
     _check(idx, got, f, oracle.as_f32(dout_raw, w.dtype), 0.5)
 
 
+@pytest.mark.parametrize("N,topk", [(4200, 100), (8300, 160), (8300, 300), (8300, 512)])
+@pytest.mark.parametrize("chunk", [0, 70])
+def test_tile_bwd_first_lists(N, topk, chunk):
+    """The gradients' first prefix list serves queries with few keys in their
+    pool, down to one: it starts two levels later than the forward's (k = 100),
+    one (160), or at the same (300, 512: a longer list would not be staged
+    whole)."""
+    w = workloads.custom(B=1, H=2, N=N, dv=32, topk=topk, dtype="bf16", bits=8, seed=topk)
+    log(f"tile bwd first lists N={N} k={topk} chunk={chunk}")
+    raw = {n: a.reshape(2, N, -1) for n, a in workloads.generate(w).items()}
+    f = {n: oracle.as_f32(a, w.dtype) for n, a in raw.items()}
+    dout_raw = workloads.generate_dout(w).reshape(2, N, w.dv)
+    idx, *got = _gpu(raw, dout_raw, w, True, 0.5, chunk=chunk)
+    _check(idx, got, f, oracle.as_f32(dout_raw, w.dtype), 0.5)
+
+
 @pytest.mark.parametrize("dv", [32, 128])
 def test_tile_bwd_nan_without_window(dv):
     """The chunked rule leaves the first chunk's queries without a window:

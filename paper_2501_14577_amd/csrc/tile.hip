@@ -360,14 +360,19 @@ __global__ void __launch_bounds__(kBndWaves * 64)
       const int32_t r0 = g_n <= kRegion || p0 <= before ? 0 : (p0 - before) & ~(kScanStep - 1);
       const int32_t r1 = r0 + kRegion < g_n ? r0 + kRegion : g_n;
       {
+        // Past the list's end its last entry is read, so that no load is under a
+        // branch (the compiler would convert and so await each one there).
         uint32_t cv[kRegion / 64];
         int32_t pv[kRegion / 64];
 #pragma unroll
         for (int t = 0; t < kRegion / 64; ++t) {
-          const int32_t e = r0 + t * 64 + lane;
-          cv[t] = e < r1 ? g_codes[e] : 0u;
-          pv[t] = e < r1 ? g_pos[e] : INT32_MAX;  // past the list's end: in no pool
+          const int32_t e = r0 + t * 64 + lane, ec = e < r1 ? e : r1 - 1;
+          cv[t] = g_codes[ec];
+          pv[t] = g_pos[ec];
         }
+#pragma unroll
+        for (int t = 0; t < kRegion / 64; ++t)
+          if (r0 + t * 64 + lane >= r1) pv[t] = INT32_MAX;  // in no pool
         const int slot16 = pos16_slot(lane % kScanStep);
 #pragma unroll
         for (int t = 0; t < kRegion / 64; ++t) {

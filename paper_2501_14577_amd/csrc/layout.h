@@ -71,9 +71,18 @@ constexpr int kMaxLevels = 32;
 // List entries the window search stages in LDS for a run of queries; a shorter
 // list is staged whole.
 constexpr int kBndRegion = 640;
-// Up to this many keys per segment a prefix-list tile counts the earlier tiles'
-// entries itself.
-constexpr int64_t kListInline = 4096;
+// Whether a prefix-list tile counts the earlier tiles' entries itself.  The
+// last tile's wavefronts read them in batches of 8 chunks of 64 each and count
+// every level in every batch; the launch saved is worth 4-5 us.  One batch of 11
+// levels is even with it (128 x 2048, k 1), two batches of 6 too (8 x 4096, k 64),
+// two of 12 lose (8 x 4096, k 1, 23.8 -> 26.5 us), and so do more keys (a forward of
+// 96 x 8192: 203.7 -> 205.7 us).
+inline bool list_inline(int64_t N, int levels) {
+  if (N > 4096) return false;
+  const int64_t earlier = (ceil_div(N, kSortTile) - 1) * kSortTile;
+  const int64_t batches = ceil_div(earlier, int64_t(kSortThreads) * 8);
+  return batches * levels <= 11;
+}
 
 // ---- attend ---------------------------------------------------------------
 constexpr int kAttWavesPerBlock = 8;

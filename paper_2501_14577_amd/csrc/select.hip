@@ -15,7 +15,7 @@
 //
 // Kernels:
 //   list_count:   per tile of the sorted list, how many keys fall in each F_t
-//                 (segments of up to kListInline keys leave it out: their few
+//                 (short segments leave it out, see list_inline: their few
 //                 tiles count the earlier entries themselves);
 //   list_scatter: stable compaction of each tile into every F_t it feeds
 //                 (one ballot per level and 64 keys; earlier tiles' counts
@@ -256,10 +256,7 @@ hipError_t launch_prefix_lists(const uint32_t* sorted_codes, const int32_t* perm
   int32_t* lpos = reinterpret_cast<int32_t*>(wsb + ws.pos_off);
   const int64_t tiles = ceil_div(N, kSortTile);
   const dim3 grid(unsigned(S * tiles)), block(kSortThreads);
-  // Counting the earlier entries again costs a tile up to 48 chunks of 64 at
-  // 4096 keys, the launch it saves 4-5 us; at 8192 keys the two are even or worse
-  // (a forward of 96 x 8192: 205.7 against 203.7 us).
-  if (N <= kListInline)
+  if (list_inline(N, lp.levels))
     cnt = nullptr;
   else
     hipLaunchKernelGGL(list_count_kernel, grid, block, 0, stream, perm, N, tiles, lp.t0, lp.levels, cnt);

@@ -368,15 +368,17 @@ __global__ void __launch_bounds__(kBndWaves * 64)
         for (int t = 0; t < kRegion / 64; ++t) {
           const int32_t e = r0 + t * 64 + lane, ec = e < r1 ? e : r1 - 1;
           cv[t] = g_codes[ec];
-          pv[t] = g_pos[ec];
+          pv[t] = causal ? g_pos[ec] : 0;
         }
 #pragma unroll
         for (int t = 0; t < kRegion / 64; ++t)
           if (r0 + t * 64 + lane >= r1) pv[t] = INT32_MAX;  // in no pool
         const int slot16 = pos16_slot(lane % kScanStep);
 #pragma unroll
+        for (int t = 0; t < kRegion / 64; ++t) s_bnd_codes[wave][t * 64 + lane] = cv[t];
+#pragma unroll
         for (int t = 0; t < kRegion / 64; ++t) {
-          s_bnd_codes[wave][t * 64 + lane] = cv[t];
+          if (!causal) break;  // no position is tested
           if constexpr (kPos16)  // positions < 65536; past the list's end: counted out by pool_bits
             s_bnd_pos16[wave][(2 * t + lane / kScanStep) * kPos16Stride + slot16] = uint16_t(uint32_t(pv[t]) ^ 0x8000u);
           else
@@ -424,8 +426,14 @@ __global__ void __launch_bounds__(kBndWaves * 64)
       L.r0 = staged ? r0 : 0;
       L.r1 = staged ? r1 : 0;
 
-      // The window, entry by entry.
-      if (go) {
+      if (go && !causal) {
+        // Every entry is in the pool: the window follows from p.
+        const int32_t m = topk < L.n ? topk : L.n;
+        const int32_t s = p - topk / 2 > 0 ? p - topk / 2 : 0;
+        const int32_t a = s < L.n - m ? s : L.n - m;
+        res = make_int2(a, a + m - 1);
+      } else if (go) {
+        // The window, entry by entry.
         const int half = topk / 2;
         const int need_r = topk - half;
         // Right side: first and last entry taken; left side: nearest and

@@ -213,11 +213,18 @@ __device__ __forceinline__ uint32_t pool_bits(const LaneList& L, int32_t B) {
   } else {
     using G = __attribute__((address_space(1))) const int32_t;
     G* gp = (G*)L.pos;
+    // Eight loads in flight at a time: left alone, the compiler waits for each
+    // (96 x 8192, k 64, random order, indices 571 -> 376 us; 8 x 20011, k 64, 66.7 ->
+    // 52.7; 512 x 1024, k 256, random order, 533 -> 472).
 #pragma unroll
-    for (int j = 0; j < kScanStep; ++j) {
-      const int32_t x = B + j;
-      const int32_t v = gp[x < 0 ? 0 : (x < L.n ? x : L.n - 1)];
-      mask = __builtin_amdgcn_alignbit(mask, (x >= 0 && x < L.n) ? uint32_t(v) + nl : 0u, 31);
+    for (int j = 0; j < kScanStep; j += 8) {
+      int32_t v[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v[t] = gp[B + j + t < L.n ? B + j + t : L.n - 1];
+      asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]));
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+        mask = __builtin_amdgcn_alignbit(mask, B + j + t < L.n ? uint32_t(v[t]) + nl : 0u, 31);
     }
   }
   return mask;

@@ -454,7 +454,7 @@ constexpr int kMergeThreads = 256;
 
 __global__ void __launch_bounds__(kMergeThreads)
     merge_runs_kernel(const uint32_t* __restrict__ run_keys, const int32_t* __restrict__ run_pos, int64_t N,
-                      int64_t blocks_per_seg, uint32_t* __restrict__ keys_out, int32_t* __restrict__ pos_out) {
+                      int64_t blocks_per_seg, uint32_t code_mask, uint32_t* __restrict__ keys_out, int32_t* __restrict__ pos_out) {
   const int64_t blk = xcd_contiguous_block(blockIdx.x, gridDim.x);
   const int64_t seg = blk / blocks_per_seg;
   const int e = int(blk - seg * blocks_per_seg) * kMergeThreads + int(threadIdx.x);
@@ -463,7 +463,8 @@ __global__ void __launch_bounds__(kMergeThreads)
   const int n = int(N);
   const int runs = (n + int(kMergeRun) - 1) / int(kMergeRun);
   const int mine = e / int(kMergeRun);  // the same for the whole wavefront
-  const uint32_t key = ks[e];
+  const uint32_t code = ks[e];
+  const uint32_t key = code & code_mask;  // the runs are in the order of these bits
   const int32_t pos = run_pos[seg * N + e];
   int lo[kMergeRuns];
 #pragma unroll
@@ -475,7 +476,7 @@ __global__ void __launch_bounds__(kMergeThreads)
         const int start = r * int(kMergeRun);
         const int len = n - start < int(kMergeRun) ? n - start : int(kMergeRun);
         const int at = lo[r] + step;
-        const uint32_t x = ks[start + (at <= len ? at : len) - 1];
+        const uint32_t x = ks[start + (at <= len ? at : len) - 1] & code_mask;
         if (at <= len && (x < key || (r < mine && x == key))) lo[r] = at;
       }
     }
@@ -483,7 +484,7 @@ __global__ void __launch_bounds__(kMergeThreads)
   int rank = e - mine * int(kMergeRun);
 #pragma unroll
   for (int r = 0; r < kMergeRuns; ++r) rank += lo[r];
-  keys_out[seg * N + rank] = key;
+  keys_out[seg * N + rank] = code;
   pos_out[seg * N + rank] = pos;
 }
 
@@ -548,7 +549,7 @@ hipError_t launch_sort(const uint32_t* k_codes, int64_t S, int64_t N, int code_b
                        run_pos);
     const int64_t bps = ceil_div(N, int64_t(kMergeThreads));
     hipLaunchKernelGGL(merge_runs_kernel, dim3(unsigned(S * bps)), dim3(kMergeThreads), 0, stream, run_keys, run_pos, N,
-                       bps, sorted_codes, perm);
+                       bps, ~0u >> (32 - code_bits), sorted_codes, perm);
     return hipGetLastError();
   }
   char* wsb = static_cast<char*>(workspace);

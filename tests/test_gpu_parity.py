@@ -221,6 +221,20 @@ def test_sort_and_order_workgroup_edges(N, S):
     assert np.array_equal(host(same), want)
 
 
+@pytest.mark.parametrize("N", [3000, 10007, 20011, 40000])
+@pytest.mark.parametrize("code_bits", [5, 18, 30])
+def test_sort_by_low_bits(N, code_bits):
+    """The order is that of the low code_bits bits alone on every path (whole
+    segments, merged runs, tiled passes); the codes come back whole."""
+    log(f"sort by low bits N={N} bits={code_bits}")
+    kc = workloads.random_codes(N + code_bits, (2, N), 32)
+    perm_want = np.argsort(kc & np.uint32((1 << code_bits) - 1), axis=1, kind="stable")
+    sc, perm = zeta.zeta_sort_keys(u32_to_dev(kc), code_bits)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(perm), perm_want)
+    assert np.array_equal(host(sc), np.take_along_axis(kc, perm_want, axis=1))
+
+
 @pytest.mark.parametrize("S,N,code_bits,high_values", [(2, 20000, 18, 4), (1, 9000, 18, 1), (3, 4097, 16, 2)])
 def test_sort_clustered(S, N, code_bits, high_values):
     """Codes whose high digit takes only a few values (one value: every key

@@ -57,11 +57,12 @@ inline bool block_sort_path(int64_t S, int64_t N) { return N <= 8192 || (N <= 16
 // times the other runs); tiled passes cost 11 us each while they are bound by
 // their launches.  Measured, passes -> merge: 30 bits, 32 x 10007 44.3 -> 28.2, 16 x
 // 20011 44.5 -> 32.8, 32 x 20011 46.7 -> 44.0, 16 x 32768 45.2 -> 45.8; 18 bits, 16
-// x 16384 23.7 -> 21.9, 16 x 20011 23.8 -> 25.7 us.
+// x 16384 23.7 -> 21.9 us.  Two passes lose to it beyond four runs however few the
+// segments (one of 20011 22.9 -> 25.7, of 32768 23.6 -> 35.7 us).
 constexpr int64_t kMergeRun = 4096;
 constexpr int kMergeRuns = 8;
 inline bool merge_sort_path(int64_t S, int64_t N, int passes) {
-  if (passes < 2 || N <= 8192 || N > kMergeRun * kMergeRuns) return false;
+  if (passes < 2 || N <= 8192 || N > kMergeRun * (passes > 2 ? kMergeRuns : 4)) return false;
   const int64_t searches = N * (ceil_div(N, kMergeRun) - 1);  // per segment
   return S <= (passes > 2 ? 5 << 19 : 3 << 18) / searches;
 }

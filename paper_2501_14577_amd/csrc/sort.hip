@@ -283,7 +283,8 @@ __global__ void __launch_bounds__(kRadixThreads)
 // Elements past the segment's end carry an all-ones key: they stay last in
 // every pass.  kByLevel: one pass over the level class of the carried
 // positions (the level partition of a processing order), which are the keys
-// here and the only output.
+// here and the only output; vals may be pos_out (every read is before the
+// first write).
 //
 // Bound: one CU's vector issue and LDS latency (a pass costs a wavefront KPT
 // times about 45 instructions and a dependent LDS count, and 4 barriers); most
@@ -293,15 +294,14 @@ __global__ void __launch_bounds__(kRadixThreads)
 // level partition, 8192 x 256, 18.8 -> 10.7.
 template <int THREADS, int KPT, bool kByLevel>
 __global__ void __launch_bounds__(THREADS)
-    block_sort_kernel(const uint32_t* __restrict__ keys, const int32_t* __restrict__ vals, int64_t N, int runs,
-                      int code_bits, int digit_bits, int t0, int t_hi, int chunk, uint32_t* __restrict__ keys_out,
-                      int32_t* __restrict__ pos_out) {
+    block_sort_kernel(const uint32_t* __restrict__ keys, const int32_t* vals, int64_t N, int runs, int code_bits,
+                      int digit_bits, int t0, int t_hi, int chunk, uint32_t* __restrict__ keys_out, int32_t* pos_out) {
   constexpr int kWaves = THREADS / 64;
   constexpr int kCap = THREADS * KPT;
   static_assert(kCap <= 16384, "positions, slots and counts are 16-bit, keys and positions fit LDS");
   __shared__ __align__(16) uint32_t s_key[kCap];
   __shared__ uint16_t s_pos[kByLevel ? 1 : kCap];
-  __shared__ uint16_t s_cnt[kWaves][kRadixMax];
+  __shared__ __align__(4) uint16_t s_cnt[kWaves][kRadixMax];  // cleared in pairs
   __shared__ uint32_t s_scan[kWaves];
   const int tid = threadIdx.x;
   const int lane = tid & 63;

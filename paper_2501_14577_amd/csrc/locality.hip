@@ -14,9 +14,10 @@
 //     compacted into LDS, the kn-th smallest is found by bisection on the bits
 //     (about 10 counts: it ends as soon as exactly kn distances lie below),
 //     and one 64-lane bitonic sort orders them.
-//   exact_knn (kn > 64, where that bound does not hold): one workgroup per
-//     query packs (distance, position) into 64-bit words and sorts up to 4096
-//     of them in LDS by a bitonic network.
+//   exact_knn (kn > 64, where that bound does not hold, and a few hundred
+//     queries over at most 256 keys): one workgroup per query packs (distance,
+//     position) into 64-bit words and sorts up to 4096 of them in LDS by a
+//     bitonic network.
 //   index_overlap: one wavefront per row marks row b's entries in an LDS
 //     bit set of the segment's positions, counts row a's marked entries, and
 //     clears its marks again.
@@ -282,7 +283,13 @@ hipError_t knn_wave_t(const T* q, const T* k, int64_t S, int64_t N, int dk, int 
   const dim3 grid(unsigned(ceil_div(rows, int64_t(kKnnWaves)))), block(kKnnWaves * 64);
 #define ZETA_KNN_WAVE(M) \
   hipLaunchKernelGGL((knn_wave_kernel<T, DK, M>), grid, block, 0, stream, q, k, rows, N, dk, kn, causal, out)
-  if (N <= 512)
+  // Every lane loads M keys, whether it holds them or not (a segment of 64 keys, d_k
+  // 8: 12.6 us with M = 8, 8.0 with 1).
+  if (N <= 64)
+    ZETA_KNN_WAVE(1);
+  else if (N <= 256)
+    ZETA_KNN_WAVE(4);
+  else if (N <= 512)
     ZETA_KNN_WAVE(8);
   else if (N <= 1024)
     ZETA_KNN_WAVE(16);
@@ -300,7 +307,11 @@ hipError_t knn_t(const void* q, const void* k, int64_t S, int64_t N, int dk, int
   static_assert(kKnnMaxN <= 64 * 64, "a lane of knn_wave holds up to 64 distances");
   const T* qq = static_cast<const T*>(q);
   const T* kk = static_cast<const T*>(k);
-  if (kn <= kKnnMaxWave) {
+  // Few queries over few keys leave the chip idle, and a workgroup has its query
+  // done sooner: 8.0 us against 8.7-9.8 for 4 segments of 100 keys, 8.6 against up to
+  // 9.5 for 5 of 128; 3 of 256 take 9.7-12.5 against 8.3-9.6.
+  const bool idle = N <= 256 && S * N <= 640;
+  if (kn <= kKnnMaxWave && !idle) {
     if (dk == 3) return knn_wave_t<T, 3>(qq, kk, S, N, dk, kn, causal ? 1 : 0, out, stream);
     return knn_wave_t<T, 0>(qq, kk, S, N, dk, kn, causal ? 1 : 0, out, stream);
   }

@@ -65,6 +65,20 @@ def test_exact_knn_ties(N, kn, causal):
     assert np.array_equal(got[:, rows], want)
 
 
+@pytest.mark.parametrize("S,N,kn", [(10, 64, 64), (11, 64, 5), (10, 65, 64), (4, 200, 64), (3, 256, 64), (2, 256, 64),
+                                    (3, 257, 64)])
+@pytest.mark.parametrize("dk", [3, 8])
+def test_exact_knn_short_segments(S, N, kn, dk):
+    """Segments of up to 256 keys, on both sides of the number of queries from
+    which a wavefront takes each (640), with many ties."""
+    log(f"exact knn short segments S={S} N={N} kn={kn} dk={dk}")
+    rng = np.random.default_rng([S, N, kn, dk])
+    q, k = (rng.integers(0, 5, size=(1, S, N, dk)).astype(np.float32) for _ in range(2))
+    for causal in (False, True):
+        got = host(zeta.zeta_exact_knn(to_dev(q, "f32"), to_dev(k, "f32"), kn, causal)).reshape(S, N, kn)
+        assert np.array_equal(got, oracle.exact_knn(q[0], k[0], kn, causal, rows=np.arange(N)))
+
+
 @pytest.mark.parametrize("N,kn", [(200, 64), (2048, 64), (500, 65)])
 def test_exact_knn_nan(N, kn):
     """Keys with a NaN of either sign or payload come after every other key,

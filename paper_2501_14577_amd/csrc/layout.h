@@ -307,11 +307,11 @@ inline QueryOrderWs query_order_ws(int64_t S, int64_t N) {
 }
 
 // Gradients of the bfloat16 one-pass attention: the one-pass call's lists,
-// bounds and key rows, then per slot a 32-byte record and the deps part, each
-// tile's window range per list and their envelopes,
-// each chunk's candidate tiles (in the envelopes' layout), the block sums of
-// deps and, with the history-mean candidate, the gradients reaching the means
-// and their scan's sums.
+// bounds and key rows, then each slot's 32-byte record, each tile's part of deps,
+// its window range per list and their envelopes, each chunk's candidate tiles (in
+// the envelopes' layout), the block sums of deps and, with the history-mean
+// candidate, the gradients reaching the means and their scan's sums.  (The key
+// pass may read up to 15 records past the last one, within this buffer.)
 constexpr int64_t kTileBwdRedPer = 4096;  // deps parts per block sum (at least)
 constexpr int64_t kTileBwdRedMax = 512;  // block sums (64-bit) at most
 // The gradients' own prefix lists start up to two levels later than the
@@ -345,7 +345,7 @@ inline TileBwdWs tile_bwd_ws(int64_t S, int64_t N, int dv, int topk, int causal,
   const size_t env = size_t(tile_bwd_levels(N, topk, causal != 0)) * tiles * 2 * sizeof(int32_t);
   w.rec_off = align_up(w.fused.bytes);
   w.part_off = w.rec_off + align_up(rows * 32);
-  w.env_off = w.part_off + align_up(rows * sizeof(float));
+  w.env_off = w.part_off + align_up(tiles * sizeof(float));
   w.env2_off = w.env_off + align_up(env);
   w.ranges_off = w.env2_off + align_up(env);
   w.sums_off = w.ranges_off + align_up(env);
@@ -358,9 +358,6 @@ inline TileBwdWs tile_bwd_ws(int64_t S, int64_t N, int dv, int topk, int causal,
     w.hist_scan_off = w.hist_v_off + align_up(rows * size_t(dv) * sizeof(float));
     w.bytes = w.hist_scan_off + hist_ws(S, N, 3 + dv).bytes;
   }
-  // The size callers know for this call also holds a copy of the dout rows;
-  // that room is unused since the key pass gathers the rows itself.
-  w.bytes += align_up(rows * size_t(dv) * 2);
   return w;
 }
 

@@ -392,12 +392,14 @@ def test_select_attend_bwd_workspace_size():
     assert ws(1, 1, 10, 64, 0, 1) == 0
     assert ws(1, 1, 10, 48, 4, 1) == 0
     assert zeta.load_library().zeta_select_attend_bwd_workspace_size(1, 1, 10, 64, 4, 2, 0) == 0  # causal not 0/1
-    # Long-context shape: the one-pass call's buffers plus, per row, the
-    # 32-byte record, the dout copy (2 x 128 B) and the deps part.
+    # Long-context shape: the one-pass call's buffers (per row at least 8 bytes
+    # of window bounds, 8 of a key row and, over the prefix lists, 16 an entry)
+    # and the 32-byte records; d_v takes no room without the history mean.
     big = ws(1, 16, 65536, 128, 128, 1)
     rows = 16 * 65536
-    assert big >= rows * (32 + 256 + 4)
-    assert big < rows * (32 + 256 + 4) + (96 << 20)
+    assert big >= rows * (32 + 32)
+    assert big < rows * 32 + (56 << 20)
+    assert big == ws(1, 16, 65536, 32, 128, 1)
     assert big % 256 == 0
     assert ws(1, 1, 1, 32, 1, 0) > 0
     # The history-mean candidate adds (3 + 128) x 4 B per row and the scan's sums.

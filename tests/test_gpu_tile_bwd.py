@@ -338,3 +338,28 @@ def test_tile_bwd_history_widths(dv, causal):
     _close(dk.reshape(rk.shape), rk, "dk")
     _close(dv_.reshape(rv.shape), rv, "dv")
     assert abs(float(deps[0]) - reps) <= 1e-4 * (1.0 + abs(reps)), (float(deps[0]), reps)
+
+
+@pytest.mark.parametrize("N,topk,dv,causal,history", [(1, 1, 32, True, False), (1000, 16, 64, True, False), (4113, 100, 128, True, True),
+                                                      (4113, 100, 32, False, True), (700, 1024, 256, True, False),
+                                                      (131073, 8, 32, True, False)])
+def test_tile_bwd_workspace_bound(N, topk, dv, causal, history):
+    """The call stays within the size it asks for, and its results do not
+    depend on what the buffer held."""
+    w = workloads.custom(B=1, H=2, N=N, dv=dv, topk=topk, dtype="bf16", bits=8, seed=N)
+    log(f"tile bwd workspace bound N={N} k={topk} dv={dv} causal={causal} history={history}")
+    q, k, v = (to_dev(a.reshape(1, 2, N, -1), w.dtype) for a in workloads.generate(w).values())
+    dout = to_dev(workloads.generate_dout(w).reshape(1, 2, N, dv), w.dtype)
+    res = zeta.forward(q, k, v, topk, 0.5, causal, w.bits, fused=True, history=history, return_intermediates=True)
+    n = zeta.zeta_select_attend_bwd_workspace_size(1, 2, N, dv, topk, causal, history)
+    runs = []
+    for fill in (0x00, 0xFF):
+        buf = torch.full((n + 8192,), fill, dtype=torch.uint8, device=device())
+        g = zeta.zeta_select_attend_bwd(q, k, v, res["q_codes"], res["sorted_codes"], res["perm"], topk, causal, 0.5, dout,
+                                        q_order=res["q_order"], mean_k=res["mean_k"], mean_v=res["mean_v"],
+                                        workspace=buf[:n])
+        torch.cuda.synchronize()
+        assert bool((buf[n:] == fill).all())
+        runs.append([host(t) for t in g])
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b) and np.isfinite(a).all()

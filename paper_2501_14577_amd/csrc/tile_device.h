@@ -61,28 +61,6 @@ __device__ __forceinline__ T* readlane_ptr(T* p, int src) {
   return (T*)g;
 }
 
-// E consecutive bfloat16 elements (E / 2 words) from a 2E-byte aligned address.
-template <int W>
-__device__ __forceinline__ void load_words(const uint16_t* p, uint32_t (&o)[W]) {
-  if constexpr (W % 4 == 0) {
-#pragma unroll
-    for (int t = 0; t < W / 4; ++t) {
-      const uint4 x = reinterpret_cast<const uint4*>(p)[t];
-      o[4 * t] = x.x;
-      o[4 * t + 1] = x.y;
-      o[4 * t + 2] = x.z;
-      o[4 * t + 3] = x.w;
-    }
-  } else if constexpr (W == 2) {
-    const uint2 x = *reinterpret_cast<const uint2*>(p);
-    o[0] = x.x;
-    o[1] = x.y;
-  } else {
-    static_assert(W == 1, "unsupported row slice");
-    o[0] = *reinterpret_cast<const uint32_t*>(p);
-  }
-}
-
 constexpr int kChunk = 16;  // rows (list entries, or a tile's queries) per product step
 
 // Value rows reach the matrix cores through LDS.  Per chunk of 16 entries the
@@ -240,54 +218,6 @@ __device__ __forceinline__ void read_rows16(const uint32_t (&addr)[8], u32x4_t (
   for (int i = 0; i < 4; ++i) {
     o[i] = o0[i];
     o[4 + i] = o1[i];
-  }
-}
-
-// Two transposing reads (as in read_tr_issue) of each of N addresses + kOff,
-// waited for in the same statement; a[i]: the fragment of addr[i], twice.
-template <uint32_t kOff>
-__device__ __forceinline__ void read_tr_pair(uint32_t a0, uint32_t a1, bf16x8_t& f0, bf16x8_t& f1) {
-  s16x4_t x, y, z, w;
-  asm volatile(
-      "ds_read_b64_tr_b16 %0, %4 offset:%6\n\t"
-      "ds_read_b64_tr_b16 %1, %4 offset:%6\n\t"
-      "ds_read_b64_tr_b16 %2, %5 offset:%6\n\t"
-      "ds_read_b64_tr_b16 %3, %5 offset:%6\n\t"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(x), "=&v"(y), "=&v"(z), "=&v"(w)
-      : "v"(a0), "v"(a1), "n"(kOff)
-      : "memory");
-  f0 = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
-  f1 = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(z, w, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
-template <uint32_t kOff, int N>
-__device__ __forceinline__ void read_tr_wait2(const uint32_t (&addr)[N], bf16x8_t (&a)[N]) {
-  static_assert(N % 2 == 0, "read in pairs");
-  if constexpr (N % 4 == 0) {
-#pragma unroll
-    for (int i = 0; i < N; i += 4) {
-      s16x4_t x[8];
-      asm volatile(
-          "ds_read_b64_tr_b16 %0, %8 offset:%12\n\t"
-          "ds_read_b64_tr_b16 %1, %8 offset:%12\n\t"
-          "ds_read_b64_tr_b16 %2, %9 offset:%12\n\t"
-          "ds_read_b64_tr_b16 %3, %9 offset:%12\n\t"
-          "ds_read_b64_tr_b16 %4, %10 offset:%12\n\t"
-          "ds_read_b64_tr_b16 %5, %10 offset:%12\n\t"
-          "ds_read_b64_tr_b16 %6, %11 offset:%12\n\t"
-          "ds_read_b64_tr_b16 %7, %11 offset:%12\n\t"
-          "s_waitcnt lgkmcnt(0)"
-          : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
-          : "v"(addr[i]), "v"(addr[i + 1]), "v"(addr[i + 2]), "v"(addr[i + 3]), "n"(kOff)
-          : "memory");
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        a[i + j] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(x[2 * j], x[2 * j + 1], 0, 1, 2, 3, 4, 5, 6, 7));
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < N; i += 2) read_tr_pair<kOff>(addr[i], addr[i + 1], a[i], a[i + 1]);
   }
 }
 

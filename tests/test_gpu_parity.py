@@ -563,6 +563,37 @@ def test_select_runs_over_several_lists(N, topk, causal, chunk):
         assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("N,topk", [(1, 3), (63, 1), (65, 2), (641, 7), (700, 700), (700, 1024), (3000, 161), (70001, 64)])
+def test_select_without_mask(N, topk):
+    """Calls that are not causal, from one key to more than 65536, windows cut
+    off at either end (codes below and above every key's), as long as the
+    segment or longer."""
+    log(f"select without mask N={N} k={topk}")
+    rng = np.random.default_rng([N, topk])
+    qc = workloads.random_codes(N, (2, N), 14)
+    kc = workloads.random_codes(N + 1, (2, N), 13) + np.uint32(1 << 12)
+    want = oracle.select_topk(qc, kc, topk, False)
+    esc, eperm = oracle.sort_keys(kc)
+    zorder = np.argsort(qc, axis=1, kind="stable").astype(np.int32)
+    shuffled = np.stack([rng.permutation(N) for _ in range(2)]).astype(np.int32)
+    for order in (i32_to_dev(zorder), i32_to_dev(shuffled), None):
+        got = host(zeta.zeta_select_topk(u32_to_dev(qc), u32_to_dev(esc), i32_to_dev(eperm), topk, False, q_order=order))
+        assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("N,topk", [(1025, 1), (3072, 1), (3072, 2), (3073, 64), (4096, 64), (4096, 65), (4097, 65)])
+def test_select_list_counts(N, topk):
+    """Lengths and numbers of prefix lists on both sides of where a list's
+    tiles count the earlier entries themselves."""
+    log(f"select list counts N={N} k={topk}")
+    qc, kc = (workloads.random_codes(N + i, (2, N), 12) for i in range(2))
+    esc, eperm = oracle.sort_keys(kc)
+    zorder = np.argsort(qc, axis=1, kind="stable").astype(np.int32)
+    order = zeta.zeta_query_order(i32_to_dev(zorder), N, 2, topk, True)
+    got = host(zeta.zeta_select_topk(u32_to_dev(qc), u32_to_dev(esc), i32_to_dev(eperm), topk, True, q_order=order))
+    assert np.array_equal(got, oracle.select_topk(qc, kc, topk, True))
+
+
 # ----------------------------------------------------------------------------
 # Query order by list level
 # ----------------------------------------------------------------------------

@@ -252,6 +252,53 @@ def test_tile_bwd_orders_and_repeat():
         assert np.array_equal(np.asarray(runs["level"][t]), np.asarray(again[t])), t
 
 
+@pytest.mark.parametrize("order", ["level", "position", "random"])
+@pytest.mark.parametrize("dv,N,causal", [(64, 8200, True), (64, 8200, False), (128, 4113, True)])
+def test_tile_bwd_two_chunks(dv, N, causal, order):
+    """Enough rows that a wavefront of the key pass takes two chunks of the
+    long lists and one of the short ones, an odd number of chunks, at the value
+    widths the workloads train with, in each kind of processing order."""
+    w = workloads.custom(B=1, H=8, N=N, dv=dv, topk=32, dtype="bf16", bits=10, seed=dv + N)
+    log(f"tile bwd two chunks dv={dv} N={N} causal={causal} order={order}")
+    raw = {n: a.reshape(8, N, -1) for n, a in workloads.generate(w).items()}
+    f = {n: oracle.as_f32(a, w.dtype) for n, a in raw.items()}
+    dout_raw = workloads.generate_dout(w).reshape(8, N, dv)
+    rng = np.random.default_rng(N)
+    given = np.stack([rng.permutation(N) for _ in range(8)]).astype(np.int32) if order == "random" else order
+    idx, *got = _gpu(raw, dout_raw, w, causal, 0.5, order=given)
+    _check(idx, got, f, oracle.as_f32(dout_raw, w.dtype), 0.5)
+
+
+def test_tile_bwd_deps_many_tiles():
+    """deps over more than 131072 tiles (summed in two stages), with values and
+    upstream gradients that give every query's part the same sign: dout_i . v_j
+    falls with |q_i - k_j|^2, so a missing or repeated part shows.  The
+    reference sums the definition in float64 over the same windows."""
+    B, H, N, dv, topk = 1, 2100, 1024, 32, 4
+    log(f"tile bwd deps over {H * N // 16} tiles")
+    g = torch.Generator(device=device()).manual_seed(3)
+    q, k = (torch.randn((B, H, N, 3), generator=g, device=device()).to(torch.bfloat16) for _ in range(2))
+    v, dout = (torch.zeros((B, H, N, dv), dtype=torch.bfloat16, device=device()) for _ in range(2))
+    v[..., :3], v[..., 3], v[..., 4] = k, -0.5 * k.float().square().sum(-1), 1
+    dout[..., :3], dout[..., 3], dout[..., 4] = q, 1, -0.5 * q.float().square().sum(-1)
+    res = zeta.forward(q, k, v, topk, 0.5, False, 10, fused=True, return_intermediates=True)
+    deps = zeta.zeta_select_attend_bwd(q, k, v, res["q_codes"], res["sorted_codes"], res["perm"], topk, False, 0.5, dout,
+                                       q_order=res["q_order"])[3]
+    ref, parts = 0.0, []
+    for s in range(0, H, 300):
+        Q, K, V, D = (t[0, s:s + 300].double() for t in (q, k, v, dout))
+        at = res["idx"][0, s:s + 300].long().reshape(len(Q), -1, 1)
+        Kj, Vj = (t.gather(1, at.expand(-1, -1, t.shape[-1])).view(len(Q), N, topk, -1) for t in (K, V))
+        S = 1 / ((Q[:, :, None] - Kj).square().sum(-1) + 0.5)
+        Z = S.sum(-1, keepdim=True)
+        p = (Vj * D[:, :, None]).sum(-1)
+        part = -((p - (S / Z * p).sum(-1, keepdim=True)) * S.square() / Z).sum(-1)
+        parts.append(float((part > 0).double().mean()))
+        ref += float(part.sum())
+    assert max(parts) < 0.01, "all but a few parts are negative"
+    assert abs(float(deps[0]) - ref) <= 1e-4 * (1.0 + abs(ref)), (float(deps[0]), ref)
+
+
 def test_tile_bwd_long_context():
     """The long-context workload at full size, as the benchmark runs it: every
     gradient matches zeta_topk_attn_bwd (the per-query path, pinned to the
@@ -338,6 +385,27 @@ def test_tile_bwd_history_widths(dv, causal):
     _close(dk.reshape(rk.shape), rk, "dk")
     _close(dv_.reshape(rv.shape), rv, "dv")
     assert abs(float(deps[0]) - reps) <= 1e-4 * (1.0 + abs(reps)), (float(deps[0]), reps)
+
+
+def test_tile_bwd_history_two_chunks():
+    """The history-mean candidate where a wavefront of the key pass takes two
+    chunks (d_v = 64, 8 segments of 8200 rows)."""
+    N, topk = 8200, 32
+    w = workloads.custom(B=1, H=8, N=N, dv=64, topk=topk, dtype="bf16", bits=10, seed=77)
+    log("tile bwd history two chunks")
+    raw = {n: a.reshape(8, N, -1) for n, a in workloads.generate(w).items()}
+    f = {n: oracle.as_f32(a, w.dtype) for n, a in raw.items()}
+    dout_raw = workloads.generate_dout(w).reshape(8, N, 64)
+    q, k, v, dout = (to_dev(a[None], w.dtype) for a in (raw["q"], raw["k"], raw["v"], dout_raw))
+    res = zeta.forward(q, k, v, topk, 0.5, True, w.bits, fused=True, history=True, return_intermediates=True)
+    grads = zeta.zeta_select_attend_bwd(q, k, v, res["q_codes"], res["sorted_codes"], res["perm"], topk, True, 0.5, dout,
+                                        q_order=res["q_order"], mean_k=res["mean_k"], mean_v=res["mean_v"])
+    torch.cuda.synchronize()
+    idx = host(res["idx"]).reshape(8, N, topk)
+    want = oracle.attend_bwd(f["q"], f["k"], f["v"], idx, 0.5, oracle.as_f32(dout_raw, w.dtype), history=True, causal=True)
+    for name, got, ref in zip(("dq", "dk", "dv"), grads, want):
+        _close(host(got).reshape(ref.shape), ref, name)
+    assert abs(float(grads[3][0]) - want[3]) <= 1e-4 * (1.0 + abs(want[3])), (float(grads[3][0]), want[3])
 
 
 @pytest.mark.parametrize("N,topk,dv,causal,history", [(1, 1, 32, True, False), (1000, 16, 64, True, False), (4113, 100, 128, True, True),

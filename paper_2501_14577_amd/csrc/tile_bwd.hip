@@ -753,17 +753,17 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
     const int2* ev = env + (int64_t(li) * S + seg) * ct;
     const int2* rgs = ranges + (int64_t(li) * S + seg) * ct;
     // The candidate ranges grow with the chunk.
-    const int64_t ta = rgs[c].x, tb = rgs[c + SUB - 1 < cl ? c + SUB - 1 : cl - 1].y;
+    const int ta = rgs[c].x, tb = rgs[c + SUB - 1 < cl ? c + SUB - 1 : cl - 1].y;
     const SlotRec* rseg = rec + seg * N;
     const unsigned char* dbytes = reinterpret_cast<const unsigned char*>(dout + seg * N * DV);
 
     // The tiles whose windows meet the chunks, 64 candidates tested at once;
     // `every`: the tile returned meets every chunk, not some only.
-    int64_t blk_base = ta, cur_base = ta;
+    int blk_base = ta, cur_base = ta;
     uint64_t pend = 0ull, in_every = 0ull;
     auto next_tile = [&](bool& every) -> int32_t {
       while (pend == 0ull && blk_base < tb) {
-        const int64_t tl = blk_base + lane;
+        const int tl = blk_base + lane;
         const int2 rg = tl < tb ? ev[tl] : make_int2(INT32_MAX, INT32_MIN);
         pend = wave_ballot((rg.x <= hi_c) & (rg.y >= lo_c));
         if (SUB > 1) in_every = wave_ballot((rg.x < lo_c + kBtChunk) & (rg.y >= lo_c + (SUB - 1) * kBtChunk));
@@ -774,7 +774,7 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
       const int b = __ffsll((unsigned long long)pend) - 1;
       pend &= pend - 1ull;
       every = SUB == 1 || ((in_every >> b) & 1ull) != 0ull;
-      return int32_t(cur_base) + b;
+      return cur_base + b;
     };
     // Half a record per lane (lanes 0..31; the others repeat them): q, list,
     // 1/Z, c on even lanes, window, pool limit and position on odd ones.  (The

@@ -57,12 +57,10 @@ namespace {
 constexpr int kBtWaves = 4;          // wavefronts per block
 constexpr int kBtChunk = kChunk;      // list entries per product step
 constexpr int kRedThreads = 1024;
-constexpr uint32_t kNoList = 0x7FFFu;    // list index of a slot whose query has no window
-constexpr uint32_t kNonFinite = 0x8000u;  // beside the list index: weight 0 times this query's terms may be NaN
+constexpr uint32_t kNoList = 0xFFFFu;  // record of a slot whose query has no window
 
 // What the key pass needs of a slot's query, in 32 bytes: q as bfloat16 bits,
-// the list index (kNoList: no window; with kNonFinite when q, or dout or a
-// value row by way of c, is not finite), 1/Z, c, the window as its first list
+// the list index (kNoList: no window), 1/Z, c, the window as its first list
 // index a and its last less a (no window: a = INT32_MIN, span = 0, which no
 // entry meets), the pool limit and the query's position.
 struct alignas(16) SlotRec {
@@ -442,12 +440,7 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
         my_deps = -inv * (xz - cc * yz);
         SlotRec r;
         r.q01 = (__float_as_uint(qv[0]) >> 16) | (__float_as_uint(qv[1]) & 0xFFFF0000u);
-        uint32_t list = mine ? uint32_t(level_index(g_lvl, causal, t0, t_hi, levels)) : kNoList;
-        // An infinite or NaN element of dout makes every dot product and so c
-        // infinite or NaN.
-        const bool finite = __builtin_isfinite(cc) && __builtin_isfinite(qv[0]) && __builtin_isfinite(qv[1]) &&
-                            __builtin_isfinite(qv[2]);
-        list |= finite ? 0u : kNonFinite;
+        const uint32_t list = mine ? uint32_t(level_index(g_lvl, causal, t0, t_hi, levels)) : kNoList;
         r.q2_list = (__float_as_uint(qv[2]) >> 16) | (list << 16);
         r.zinv = inv;
         r.c = cc;
@@ -666,7 +659,7 @@ constexpr int kKeyWaves = 4;  // wavefronts per block
 constexpr int kKeyThreads = kKeyWaves * 64;
 
 template <int DV, int SUB, bool kOff32>
-__global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_eu(DV <= 64 ? 3 : 2)))
+__global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_eu(DV <= 32 ? 4 : (DV <= 64 ? 3 : 2))))
     bwd_tile_key_kernel(const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                         const int32_t* __restrict__ sorted_pos, const int32_t* __restrict__ list_pos,
                         const uint2* __restrict__ keys_full, const uint2* __restrict__ keys_list,
@@ -757,23 +750,20 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
     const SlotRec* rseg = rec + seg * N;
     const unsigned char* dbytes = reinterpret_cast<const unsigned char*>(dout + seg * N * DV);
 
-    // The tiles whose windows meet the chunks, 64 candidates tested at once;
-    // `every`: the tile returned meets every chunk, not some only.
+    // The tiles whose windows meet the chunks, 64 candidates tested at once.
     int blk_base = ta, cur_base = ta;
-    uint64_t pend = 0ull, in_every = 0ull;
-    auto next_tile = [&](bool& every) -> int32_t {
+    uint64_t pend = 0ull;
+    auto next_tile = [&]() -> int32_t {
       while (pend == 0ull && blk_base < tb) {
         const int tl = blk_base + lane;
         const int2 rg = tl < tb ? ev[tl] : make_int2(INT32_MAX, INT32_MIN);
         pend = wave_ballot((rg.x <= hi_c) & (rg.y >= lo_c));
-        if (SUB > 1) in_every = wave_ballot((rg.x < lo_c + kBtChunk) & (rg.y >= lo_c + (SUB - 1) * kBtChunk));
         cur_base = blk_base;
         blk_base += 64;
       }
       if (pend == 0ull) return -1;
       const int b = __ffsll((unsigned long long)pend) - 1;
       pend &= pend - 1ull;
-      every = SUB == 1 || ((in_every >> b) & 1ull) != 0ull;
       return cur_base + b;
     };
     // Half a record per lane (lanes 0..31; the others repeat them): q, list,
@@ -787,34 +777,33 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
     // issued.  A query of weight 0 still enters the products and sums, where an
     // infinity or NaN would not vanish: one without a window here has q, 1/Z and
     // c zero and takes the row of the tile's first query with one.
-    // Returns whether a query of this list is not finite.
-    auto stage = [&](int32_t tau, int buf) -> bool {
-      const uint32_t pair = uint32_t(__builtin_amdgcn_update_dpp(int(st.y), int(st.y), 0xB1, 0xF, 0xF, false));
-      const uint32_t list = ((lane & 1) != 0 ? pair : st.y) >> 16;  // held by the even lane
+    auto stage = [&](int32_t tau, int buf) {
+      uint4 r = st;
+      const uint32_t pair = uint32_t(__builtin_amdgcn_update_dpp(int(r.y), int(r.y), 0xB1, 0xF, 0xF, false));
+      const uint32_t list = ((lane & 1) != 0 ? pair : r.y) >> 16;  // held by the even lane
       const bool past = tau * 16 + ((lane & 31) >> 1) >= n32;
-      if (past) st = make_uint4(0u, 0u, 0u, 0u);
-      const bool other = past || (list & ~kNonFinite) != li;
+      if (past) r = make_uint4(0u, 0u, 0u, 0u);
+      const bool other = past || list != li;
       // A visited tile has a window in this list, so such a lane exists.
       const uint64_t own = wave_ballot((lane & 1) != 0 && !other);
       const uint32_t own_row = uint32_t(
-          __builtin_amdgcn_readlane(int(st.w), own != 0ull ? __ffsll((unsigned long long)own) - 1 : 0));
+          __builtin_amdgcn_readlane(int(r.w), own != 0ull ? __ffsll((unsigned long long)own) - 1 : 0));
       if (other) {
         const bool odd = (lane & 1) != 0;
-        st.x = odd ? uint32_t(INT32_MIN) : 0u;
-        st.y = 0u;
-        st.z = odd ? st.z : 0u;
-        st.w = odd && own != 0ull ? own_row : 0u;
+        r.x = odd ? uint32_t(INT32_MIN) : 0u;
+        r.y = 0u;
+        r.z = odd ? r.z : 0u;
+        r.w = odd && own != 0ull ? own_row : 0u;
       }
-      if (lane < 32) *reinterpret_cast<uint4*>(&s_rec[wave][buf][lane >> 1][(lane & 1) * 4]) = st;
+      if (lane < 32) *reinterpret_cast<uint4*>(&s_rec[wave][buf][lane >> 1][(lane & 1) * 4]) = r;
 #pragma unroll
       for (int j = 0; j < VS::kLoads; ++j) {
-        const int32_t row = __shfl(int(st.w), copy_src + j * copy_step, 64);
+        const int32_t row = __shfl(int(r.w), copy_src + j * copy_step, 64);
         const Off boff = Off(row) * Off(VS::kRowBytes) + Off(copy_off[j]);
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(dbytes + boff),
                                          (__attribute__((address_space(3))) void*)(s_d[wave] + buf * VS::kBytes + 1024 * j),
                                          16, 0, 0);
       }
-      return (wave_ballot(list >= kNonFinite) & own) != 0ull;
     };
     // The rows' fragments of buffer `buf`, as they lie and transposed (read
     // twice, once per K half of the products).
@@ -890,16 +879,13 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
     };
     using std::integral_constant;
     using AllChunks = integral_constant<int, SUB>;
-    bool every = true, deferred = false;
-    const int32_t head = next_tile(every);
+    const int32_t head = next_tile();
     const bool touched = head >= 0;
     if (touched) {
       load_rec(head);
-      // Weight 0 times a term that is not finite is NaN: a tile that holds one
-      // must not enter a chunk it does not meet, and is left for below.
-      bool leave = stage(head, 0) && !every;
-      int32_t nxt = next_tile(every);
-      if (nxt >= 0) load_rec(nxt);
+      stage(head, 0);
+      int32_t nxt = next_tile();
+      load_rec(nxt >= 0 ? nxt : head);
       // The tile in buffer `buf` is read whole first; then the next tile's
       // copies into the other buffer are issued and the records of the one
       // after it loaded (reads issued after the copies would wait for them),
@@ -907,38 +893,50 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
       for (int buf = 0;; buf ^= 1) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this tile's rows (and the next one's records) have landed
         read_tile(buf);
-        const bool more = nxt >= 0, skip = leave;
+        const bool more = nxt >= 0;
         if (more) {
-          leave = stage(nxt, buf ^ 1) && !every;
-          nxt = next_tile(every);
-          if (nxt >= 0) load_rec(nxt);
+          stage(nxt, buf ^ 1);
+          nxt = next_tile();
+          // Loaded without a branch, which could cost a register copy and with it a
+          // wait for the load.
+          load_rec(nxt >= 0 ? nxt : head);
         }
         wave_lds_sync();
-        if (skip)
-          deferred = true;
-        else
-          sum_chunks(buf, integral_constant<int, 0>{}, AllChunks{});
+        sum_chunks(buf, integral_constant<int, 0>{}, AllChunks{});
         if (!more) break;
       }
     }
     if constexpr (SUB > 1) {
       static_assert(SUB == 2, "a tile meets both chunks or one");
-      // The tiles left out above, each into the one chunk it meets.
-      if (deferred) {
+      // Weight 0 times a term that is not finite is NaN, so a tile must not
+      // enter a chunk it does not meet when its dout or q, or the chunk's k or
+      // v, is infinite or NaN.  Each of these leaves its NaN in dk: only then
+      // are the sums formed again, tile by tile into the chunks it meets.
+      bool finite = true;
+#pragma unroll
+      for (int u = 0; u < SUB; ++u)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) finite &= __builtin_isfinite(gk[u][a]);
+      if (wave_ballot(!finite) != 0ull) {
+#pragma unroll
+        for (int u = 0; u < SUB; ++u) {
+#pragma unroll
+          for (int j = 0; j < E; ++j) acc[u][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+          for (int a = 0; a < 3; ++a) gk[u][a] = 0.0f;
+        }
         blk_base = ta;
-        for (int32_t t = next_tile(every); t >= 0; t = next_tile(every)) {
-          if (every) continue;
+        for (int32_t t = next_tile(); t >= 0; t = next_tile()) {
           load_rec(t);
-          const bool nonfinite = stage(t, 0);
+          stage(t, 0);
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
           wave_lds_sync();
-          if (nonfinite) {
-            read_tile(0);
-            if (__builtin_amdgcn_readfirstlane(ev[t].y) < lo_c + kBtChunk)
-              sum_chunks(0, integral_constant<int, 0>{}, integral_constant<int, 1>{});
-            else
-              sum_chunks(0, integral_constant<int, 1>{}, integral_constant<int, 2>{});
-          }
+          read_tile(0);
+          const int2 rg = ev[t];
+          if (__builtin_amdgcn_readfirstlane(rg.x) < lo_c + kBtChunk)
+            sum_chunks(0, integral_constant<int, 0>{}, integral_constant<int, 1>{});
+          if (__builtin_amdgcn_readfirstlane(rg.y) >= lo_c + kBtChunk)
+            sum_chunks(0, integral_constant<int, 1>{}, integral_constant<int, 2>{});
           wave_lds_sync();
         }
       }

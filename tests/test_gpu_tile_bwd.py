@@ -165,14 +165,16 @@ def test_tile_bwd_nan_without_window(dv):
             assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("what", ["dout", "q"])
 @pytest.mark.parametrize("dv", [64, 128])
-def test_tile_bwd_nonfinite_row_stays_in_its_chunks(dv):
-    """A NaN or infinite dout row of a query with a window reaches the keys of
-    the 16-entry chunks that its tile's windows meet, and no others: every key
-    outside them has the bits it has with that row zero.  Enough rows that a
-    wavefront of the key pass takes two chunks, an odd number of them."""
+def test_tile_bwd_nonfinite_row_stays_in_its_chunks(dv, what):
+    """A NaN or infinite dout (or q) row of a query with a window reaches the
+    keys of the 16-entry chunks that its tile's windows meet, and no others:
+    every key outside them has the bits it has with that row finite.  Enough
+    rows that a wavefront of the key pass takes two chunks, an odd number of
+    them."""
     w = workloads.custom(B=1, H=8, N=4112, dv=dv, topk=16, dtype="bf16", bits=8, seed=dv + 5)
-    log(f"tile bwd non-finite dout row dv={dv}")
+    log(f"tile bwd non-finite {what} row dv={dv}")
     S, N = w.segments, w.N
     q, k, v = (to_dev(a.reshape(1, S, N, -1), w.dtype) for a in workloads.generate(w).values())
     res = zeta.forward(q, k, v, w.topk, 0.5, False, w.bits, fused=True, return_intermediates=True)
@@ -181,18 +183,19 @@ def test_tile_bwd_nonfinite_row_stays_in_its_chunks(dv):
     seg = np.arange(S)
     slot = np.random.default_rng(dv).integers(0, N, S)
     dirty_q = order[seg, slot]
-    clean = workloads.generate_dout(w).reshape(S, N, dv).copy()
-    clean[seg, dirty_q] = 0
-    dirty = clean.copy()
-    dirty[seg, dirty_q] = np.where(seg % 2, 0x7FC0, 0x7F80)[:, None].astype(dirty.dtype)
+    dout = to_dev(workloads.generate_dout(w).reshape(1, S, N, dv), w.dtype)
+    dout[0, seg, dirty_q] = 0
 
-    def grads(dout):
+    def grads():
         g = zeta.zeta_select_attend_bwd(q, k, v, res["q_codes"], res["sorted_codes"], res["perm"], w.topk, False, 0.5,
-                                        to_dev(dout[None], w.dtype), q_order=res["q_order"])
+                                        dout, q_order=res["q_order"])
         torch.cuda.synchronize()
         return [host(t).reshape(S, N, -1) for t in g[:3]]
 
-    (_, ck, cv), (_, gk, gv) = grads(clean), grads(dirty)
+    _, ck, cv = grads()
+    bad = torch.tensor([float("inf"), float("nan")] * (S // 2), dtype=torch.bfloat16, device=q.device)
+    (dout if what == "dout" else q)[0, seg, dirty_q] = bad[:, None]
+    _, gk, gv = grads()
     for s in range(S):
         rank = np.empty(N, np.int64)
         rank[perm[s]] = np.arange(N)
@@ -200,7 +203,46 @@ def test_tile_bwd_nonfinite_row_stays_in_its_chunks(dv):
         chunks = rank[idx[s, tile]] // 16
         away = (rank // 16 < chunks.min()) | (rank // 16 > chunks.max())
         assert np.array_equal(gk[s, away], ck[s, away]) and np.array_equal(gv[s, away], cv[s, away]), s
-        assert not np.isfinite(gv[s, idx[s, dirty_q[s]]]).any()
+        assert not np.isfinite((gv if what == "dout" else gk)[s, idx[s, dirty_q[s]]]).any()
+
+
+@pytest.mark.parametrize("what", ["v", "k"])
+def test_tile_bwd_nonfinite_key_outside_all_windows(what):
+    """Keys in chunks that no tile's windows meet have gradients of zero
+    whatever their rows hold, also where the wavefront's other chunk is met."""
+    w = workloads.custom(B=1, H=8, N=4112, dv=64, topk=16, dtype="bf16", bits=8, seed=9)
+    log(f"tile bwd non-finite {what} row outside all windows")
+    S, N = w.segments, w.N
+    q, k, v = (to_dev(a.reshape(1, S, N, -1), w.dtype) for a in workloads.generate(w).values())
+    q *= 0.1
+    dout = to_dev(workloads.generate_dout(w).reshape(1, S, N, 64), w.dtype)
+    res = zeta.forward(q, k, v, w.topk, 0.5, False, w.bits, fused=True, return_intermediates=True)
+    order, perm = (host(res[n]).reshape(S, N) for n in ("q_order", "perm"))
+    idx = host(res["idx"]).reshape(S, N, w.topk)
+    keys = []  # (segment, position) of the keys of unmet chunks beside a met one
+    for s in range(S):
+        rank = np.empty(N, np.int64)
+        rank[perm[s]] = np.arange(N)
+        at = rank[idx[s, order[s]]].reshape(N // 16, -1) // 16
+        met = np.zeros((N // 16 + 1) // 2 * 2, bool)
+        for lo, hi in zip(at.min(1), at.max(1)):
+            met[lo:hi + 1] = True
+        alone = ~met & met.reshape(-1, 2)[:, ::-1].reshape(-1)
+        keys += [(s, perm[s, e]) for c in np.flatnonzero(alone[:N // 16]) for e in range(16 * c, 16 * c + 16)]
+    assert keys
+    at = tuple(np.array(keys).T)
+
+    def grads():
+        g = zeta.zeta_select_attend_bwd(q, k, v, res["q_codes"], res["sorted_codes"], res["perm"], w.topk, False, 0.5,
+                                        dout, q_order=res["q_order"])
+        torch.cuda.synchronize()
+        return [host(t) for t in g]
+
+    clean = grads()
+    assert not clean[1][0][at].any() and not clean[2][0][at].any()
+    (v if what == "v" else k)[0, at[0], at[1]] = float("nan")
+    for a, b in zip(clean[1:3], grads()[1:3]):
+        assert np.array_equal(a, b)
 
 
 @pytest.mark.parametrize("N,H,dv", [(1000, 2, 32), (4112, 8, 64)])

@@ -144,9 +144,11 @@ __device__ __forceinline__ void knn_select(const int (&d)[NR], int take, int lo,
   }
 }
 
-// Bound: vector issue (per query about 10 instructions per key for the
-// distance, 6 for the bound and the compaction, then about 500).  2048 keys,
-// kn 64, 16 segments: 110 us, against 2340 us with the workgroup sort above.
+// Bound: half vector issue (per query and 64 keys about 10 instructions for the
+// distances, 6 for the bound and the compaction, then about 500: 54 us of the 110
+// below), half the key loads' latency at the 3 wavefronts per SIMD that the
+// registers of 32 keys a lane leave.  2048 keys, kn 64, 16 segments: 110 us, against
+// 2340 us with the workgroup sort above.
 template <typename T, int DK, int M>
 __global__ void __launch_bounds__(kKnnWaves * 64)
     knn_wave_kernel(const T* __restrict__ q, const T* __restrict__ k, int64_t rows, int64_t N, int dk_rt, int kn,

@@ -107,12 +107,14 @@ constexpr uint32_t kIdxEmpty = 0xFFFFFFFFu;
 // range of kRegion entries around the first waiting query's insertion point is
 // copied to LDS (codes and positions) and serves every lane of that list near
 // it; the others wait for a range of their own, or, in an order without
-// locality, read the lists themselves.  Bound: vector issue when there are many
-// runs, else the latency of the slowest run: with the other lanes served by one
-// wavefront-wide search each, a run that crosses two lists held the call up by
-// 10-30 us (1024 queries, k 32: 25 -> 9 us; 8 x 20011, k 64: 66 -> 34 us; clustered
-// keys, 128 x 4096, k 64, not causal: 46 -> 25 us; runs of one list, 16 x 65536,
-// k 128: 42 us either way).
+// locality, read the lists themselves.  Without a causal mask the window follows
+// from the insertion point and no position is read.  Bound: vector issue when
+// there are many runs (81% at 16 x 65536, k 128: 43 us), else the latency of the
+// slowest run: with the other lanes served by one wavefront-wide search each, a
+// run that crosses two lists held the call up by 10-30 us (1024 queries, k 32: 25
+// -> 9 us; 8 x 20011, k 64: 64 -> 34, and 20 with eight loads in flight where
+// scans leave the copy).  Not causal: 512 x 1024, k 64, 8.9 us (14-18 with the
+// scan); clustered keys, 128 x 4096, k 64, 45 -> 24 with rounds -> 11.
 constexpr int kBndWaves = 4;
 constexpr int kRegion = kBndRegion;  // list entries staged per wavefront (a multiple of 64; 512 left more runs a second round)
 constexpr int kMargin = 192;    // at most this many of them before the leading insertion point

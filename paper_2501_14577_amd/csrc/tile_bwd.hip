@@ -141,7 +141,7 @@ __device__ __forceinline__ int level_index(int lvl, int causal, int t0, int t_hi
 // straight into LDS a chunk ahead, as in the forward, instead of gathered into
 // registers, and no copy of the dout rows is kept for the key pass (it gathers
 // them itself).  16 x 65536, k 128, d_v 128: 616 -> 400 us; 96 x 8192, k 64, d_v
-// 64: 207 -> 153 us.
+// 64: 207 -> 153 us (161 since its first lists are merged).
 template <int DV, bool kOff32, bool kHist>
 __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per_eu(DV <= 128 ? 3 : 1)))
     bwd_tile_query_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ v,
@@ -650,7 +650,8 @@ __global__ void __launch_bounds__(THREADS)
 // shared, and the longer visits outweigh the third wavefront per SIMD that one
 // chunk leaves room for (16 x 65536, k 128, d_v 128: 886 against 935 us; with the
 // barrier-coupled blocks of four chunks before, 1144 us; 96 x 8192, k 64, d_v 64:
-// 340 against 355, before 431 us).  A wavefront spends about a quarter of its time
+// 340 against 355, before 431 us; 861 and 318 us now that the first lists are
+// merged).  A wavefront spends about a quarter of its time
 // on its first dependent loads and a third on the sums; the prefix lists' adds
 // (dv read and written again) take a quarter of the call.  Persistent wavefronts
 // that prefetch the next unit were slower (1004 us: they wait for their own

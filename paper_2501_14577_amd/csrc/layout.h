@@ -50,7 +50,12 @@ constexpr int64_t kRadixInlineTiles = 32;
 // and lose on 18-bit codes and the level partition (23 -> 25, 12 -> 14 us).  At
 // 32768 keys a workgroup's registers spill and it loses at any number (46 ->
 // 100 us for 16 segments).
-inline bool block_sort_path(int64_t S, int64_t N) { return N <= 8192 || (N <= 16384 && S >= 100); }
+// One pass saves too little for that below two million keys in all (128 segments of
+// 10007, tiled pass -> one workgroup: level partition 14.5 -> 15.0 us, 9-bit codes
+// 14.5 -> 15.1; of 16384: 18.5 -> 15.5, 16.4 -> 16.5).
+inline bool block_sort_path(int64_t S, int64_t N, int passes) {
+  return N <= 8192 || (N <= 16384 && (passes > 1 ? S >= 100 : S * N >= 2 << 20));
+}
 // Whether longer segments are sorted as runs of kMergeRun keys, one workgroup
 // each, and merged.  The runs cost 17 us (30-bit codes, four passes; 10 us in
 // two passes) and the merge about 5 us and 6.5 us per million searches (elements

@@ -231,7 +231,7 @@ hipError_t launch_query_order(const int32_t* q_order, int64_t S, int64_t N, int 
   char* wsb = static_cast<char*>(workspace);
   uint32_t* phist = reinterpret_cast<uint32_t*>(wsb + ws.phist_off);
   const int32_t* given = q_order;
-  if (q_order != nullptr && q_order == order_out && !block_sort_path(S, N)) {
+  if (q_order != nullptr && q_order == order_out && !block_sort_path(S, N, 1)) {
     // In place: partition from a copy (a segment that one workgroup holds
     // is read whole before it is written).
     int32_t* copy = reinterpret_cast<int32_t*>(wsb + ws.given_off);

@@ -518,7 +518,7 @@ hipError_t launch_level_partition(const int32_t* vals, int64_t S, int64_t N, int
   const int64_t tiles = ceil_div(N, kLevelTile);
   int nbits = 1;
   while ((1 << nbits) < levels + 1) ++nbits;
-  if (block_sort_path(S, N)) {
+  if (block_sort_path(S, N, 1)) {
     launch_block_sort<true>(nullptr, vals, S, N, nbits, nbits, t0, t_hi, chunk, nullptr, vals_out, stream);
     return hipGetLastError();
   }
@@ -534,7 +534,7 @@ hipError_t launch_level_partition(const int32_t* vals, int64_t S, int64_t N, int
 hipError_t launch_sort(const uint32_t* k_codes, int64_t S, int64_t N, int code_bits,
                        uint32_t* sorted_codes, int32_t* perm, void* workspace, hipStream_t stream) {
   const SortPlan plan = sort_plan(N, code_bits);
-  if (block_sort_path(S, N)) {
+  if (block_sort_path(S, N, plan.passes)) {
     launch_block_sort<false>(k_codes, nullptr, S, N, code_bits, plan.digit_bits, 0, 0, 0, sorted_codes, perm, stream);
     return hipGetLastError();
   }

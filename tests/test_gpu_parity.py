@@ -221,6 +221,26 @@ def test_sort_and_order_workgroup_edges(N, S):
     assert np.array_equal(host(same), want)
 
 
+@pytest.mark.parametrize("N", [16383, 16384])
+def test_one_pass_many_segments(N):
+    """One-pass sorts and the level partition (in place too) of 128 segments on
+    both sides of two million keys in all, where a workgroup takes each segment."""
+    log(f"one pass, 128 segments N={N}")
+    rng = np.random.default_rng(N)
+    kc = workloads.random_codes(N, (128, N), 9)
+    esc, eperm = oracle.sort_keys(kc)
+    sc, perm = zeta.zeta_sort_keys(u32_to_dev(kc), 9)
+    z = np.stack([rng.permutation(N) for _ in range(128)]).astype(np.int32)
+    dev = i32_to_dev(z)
+    got = zeta.zeta_query_order(dev, N, 128, 16, True)
+    same = zeta.zeta_query_order(dev, N, 128, 16, True, order_out=dev)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(perm), eperm) and np.array_equal(host(sc), esc)
+    level = np.maximum(np.ceil(np.log2(z + 1)).astype(int), 4)
+    want = np.take_along_axis(z, np.argsort(level, axis=1, kind="stable"), axis=1)
+    assert np.array_equal(host(got), want) and np.array_equal(host(same), want)
+
+
 @pytest.mark.parametrize("N", [3000, 10007, 20011, 40000])
 @pytest.mark.parametrize("code_bits", [5, 18, 30])
 def test_sort_by_low_bits(N, code_bits):
